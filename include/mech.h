@@ -118,7 +118,7 @@ enum { MECH_FP64 = 0, MECH_FP32_MIXED = 1 };
  *             conductances: backward Euler of the cable equation linearised
  *             with rhs and d, (1e-3 cm/dt + d_n) dv_n + sum_j k_nj (dv_n -
  *             dv_j) = rhs_n + sum_j k_nj (v_j - v_n), k_nj = 100 g_nj/area_n,
- *             solved by Hines elimination; spikes as in ISOLATED.            */
+ *             solved by elimination along the trees; spikes as in ISOLATED.  */
 enum { MECH_V_EXTERNAL = 0, MECH_V_CLAMP = 1, MECH_V_ISOLATED = 2, MECH_V_CABLE = 3 };
 /* PLAIN: per step, one launch per mechanism type for the current update,
  *        one for the voltage, one per type for the state update, issued
@@ -203,13 +203,14 @@ int mech_cable_required_bytes(int64_t n_nodes, const int32_t *parent, int32_t un
  * order) and every cell a contiguous node range that starts at its root
  * (MECH_ERR_INVAL otherwise).  g_axial (device, double[n_nodes], caller
  * owned): the axial conductance in uS between node n and its parent.
- * unit_nodes bounds the nodes one workgroup solves together in LDS (44 B
- * per node): 0 takes the library's default of 1024, a value above the
- * device's LDS capacity (3537 nodes on gfx950) is reduced to it, a
- * negative one is MECH_ERR_INVAL.  Any bound gives the same elimination up
- * to rounding; it only changes how cells are cut.  A cell larger than the bound is cut into subtrees that
- * fit and a trunk, which is solved in global memory if it is still too
- * large (a long unbranched cell).  The library builds the elimination
+ * unit_nodes bounds the nodes one workgroup solves together in LDS (at most
+ * 64 B per node): 0 takes the library's default (cells whole if every cell
+ * fits LDS, else 1024), a value above the device's LDS capacity (2416 nodes
+ * on gfx950) is reduced to it, a negative one is MECH_ERR_INVAL.  Any bound
+ * gives the same elimination up to rounding; it only changes how cells are
+ * cut.  A cell larger than the bound is cut into subtrees that fit and a
+ * trunk, which is solved in global memory if it is still too large (a long
+ * unbranched cell).  The library builds the elimination
  * schedules into dev_buf (dev_bytes >=
  * mech_cable_required_bytes, 256-byte aligned, caller owned, MECH_ERR_NOMEM
  * if short) and computes the coupling coefficients 100 g/area from the
@@ -226,7 +227,8 @@ int mech_bind_cable(mech_ctx *ctx, const int32_t *parent, const double *g_axial,
  * pos_node, pos_par, pos_src (per position: its node, the position of its
  * parent's row in the same unit or -1, for a ghost the piece root's own
  * position else -1), elim_n, elim_p (edge records: child and parent
- * position, a root paired with itself), elim_ptr (height boundaries),
+ * position, a root paired with itself: Hines elimination by heights, an order
+ * that gives the solve's result up to rounding), elim_ptr (height boundaries),
  * unit_pos, unit_elim (per unit: position range, range into elim_ptr),
  * unit_mode (0 whole cells, 1 subtrees of a cut cell, 2 its trunk), and
  * the launch lists up, top (in LDS), top in global memory, down.  If buf is

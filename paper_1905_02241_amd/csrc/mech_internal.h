@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "mech.h"
+#include "mech_tree.h"
 
 namespace mech {
 
@@ -77,47 +78,30 @@ struct NodesDev {
     double *cai, *ica;
 };
 
-// Cell trees of the cable mode, cut into units that one workgroup solves.
-// A unit is a whole cell (FULL), a forest of subtrees whose roots hang off a
-// larger cell's trunk (PIECE), or that trunk (TOP) with the piece roots as
-// ghost rows.  Rows of the solve live at positions: every node has one, and
-// every piece root has a second one as a ghost in its trunk's unit.
-enum { kUnitFull = 0, kUnitPiece = 1, kUnitTop = 2 };
-// LDS of a unit solved there, per position: D, R and the voltage difference
-// to the parent (24 B) and one edge record (packed rows and run length, two
-// couplings: 20 B).
-constexpr int kCableLdsBytesPerNode = 44;
-// A unit solved in LDS packs each record as child row (12 bits), parent row
-// (12 bits) and run length (8 bits): at most 4095 rows, runs of up to
-// kCableRunMax children of one parent at one height per head (a longer run
-// is followed by comparing parents).
-constexpr int kCableLdsUnitMax = 4095;
-constexpr int kCableRunMax = 255;
-
+// Cell trees of the cable mode, cut into units that one workgroup solves
+// (kinds of units, positions, elimination order and tables: mech_tree.h).
 struct CableDev {
     const double *g_axial;     // uS to the parent
     const int *parent;         // [n_nodes]
-    const int *pos_node;       // [n_pos] node of each position
-    const int *pos_pnode;      // [n_pos] that node's parent node, or -1
-    const int *pos_par;        // [n_pos] position of the parent's row in the same unit, or -1
-    const int *pos_src;        // [n_pos] ghost: the piece root's own position; -1 otherwise
-    const int *elim_run;       // per record: run length at the head of a parent's run of a height, else 0
-    const int *elim_n;         // edge records: child position, per unit by the child's height
-    const int *elim_p;         // parent position
-    const int *elim_ptr;       // height boundaries into elim_n / elim_p
-    const int *unit_pos;       // [n_units + 1] position ranges
-    const int *unit_elim;      // [n_units + 1] into elim_ptr
-    const int *unit_mode;      // [n_units] kUnit*
-    const int *list_up;        // FULL and PIECE units (LDS), tallest first
-    const int *list_top;       // TOP units that fit in LDS
-    const int *list_top_g;     // TOP units solved in global scratch
-    const int *list_down;      // FULL and PIECE units, second pass (back-substitution)
-    int n_up, n_top, n_top_g, n_down;
-    int lds_max_nodes;         // largest unit solved in LDS
-    double *ekn, *ekp;         // per edge record: 100 g/area_n, 100 g/area_p
-    double *kn;                // per node: 100 g/area_n (0 at a root)
-    double *D, *R;             // per position: rows handed between passes, global-scratch units
-    double *DV;                // per position: v_parent - v_node of this step (global-scratch units)
+    // per position: its node; that node's parent node or -1; at a ghost, the
+    // piece root's own position, else -1; -1 with a parent
+    // row in the unit, else (a root) the row of its ghost in the trunk that its
+    // workgroup solves, or -2
+    const int4 *pos;
+    const TreeUnit *units;     // all units
+    // the launches' units: whole cells, pieces, and trunks that pieces solve;
+    // other trunks that fit in LDS; trunks with their rows in global memory;
+    // in pairs (piece, its trunk) and (trunk, the same)
+    const TreeUnit *units_a, *units_top, *units_top_g, *units_b;
+    const char *block;         // the units' tables
+    int n_units, n_a, n_top, n_top_g, n_b;
+    int lds_a, lds_top, lds_b; // dynamic LDS of the launches
+    int block_a, block_b;      // threads
+    double *pa, *pu;           // per position: area/100, conductance to the parent
+    // per position, four doubles between launches: a piece's rows after its
+    // rounds as quotients (its roots' as they are, then with dv), the rows of
+    // trunks that pieces solve, the rows of trunks in global memory
+    double *G;
 };
 
 struct FusedArgs {
@@ -224,7 +208,7 @@ hipError_t launch_stream(int op, int unroll, int flags, void *dst, const void *s
                          hipStream_t s);
 hipError_t launch_cable(const CableDev &c, const NodesDev &nd, const GlobDev &g, hipStream_t s);
 hipError_t cable_allow_lds(size_t bytes);
-hipError_t launch_cable_coeffs(const CableDev &c, const double *area, int n_nodes, int n_edges, hipStream_t s);
+hipError_t launch_cable_coeffs(const CableDev &c, const double *area, hipStream_t s);
 hipError_t launch_fused(bool fp32, int phases, int vmode, const FusedArgs &a, int grid, int block, int tile_nodes,
                         hipStream_t s);
 size_t fused_lds_bytes(int tile_nodes, bool ion);

@@ -18,7 +18,7 @@
 //   resident  the fused kernel's tiles kept in LDS for many steps (clamp and
 //             isolated modes), so STATEs cross HBM once per launch.
 //
-// Cable mode adds the tree solve (k_cable) between the current update and
+// Cable mode adds the tree solve (k_tree_*) between the current update and
 // the voltage.
 // The work is elementwise and exponential/division heavy (section 6 calls the
 // state kernels compute bound and the current kernels bandwidth bound); there
@@ -801,59 +801,70 @@ __global__ void k_visolated(NodesDev nd, GlobDev g) {
 }
 
 // ---------------------------------------------------------- cable solve --
-// Backward Euler of the cable equation on each cell's tree (Hines 1984).  Row
-// n of the system: D_n dv_n - k_{n,p} dv_p - sum_c k_{n,c} dv_c = R_n with
-// D_n = 1e-3 cm/dt + d_n + k_{n,p} + sum_c k_{n,c}, k_{n,j} = 100 g/area_n.
+// Backward Euler of the cable equation on each cell's tree, linearised with
+// the mechanisms' rhs and d.  Row n, scaled by a_n = area_n/100 so that both
+// ends of an edge see the same conductance g:
+//   S_n dv_n - sum_j g_nj dv_j = T_n,
+//   S_n = a_n (1e-3 cm/dt + d_n) + sum_j g_nj,
+//   T_n = a_n rhs_n + sum_j g_nj (v_j - v_n).
+// A round (mech_tree.h) eliminates rows i that have a parent p (coupling U_i)
+// and at most one child c (coupling N_i, until then U_c):
+//   S_p -= U_i^2/S_i, T_p += T_i U_i/S_i, and the same for c with N_i; c then
+//   hangs off p with U_c = N_i U_i/S_i.
+// After the last round dv = T/S at the roots, and the rounds are walked
+// backwards with dv_i = (T_i + U_i dv_p + N_i dv_c)/S_i, whose three quotients
+// are formed for all rows at once beforehand.
 //
-// Each position first writes its own row without the terms of its children:
-// D_n = 1e-3 cm/dt + d_n + k_{n,p}, R_n = rhs_n + k_{n,p} (v_p - v_n).
-// Elimination then runs by height from the leaves (a node's height is one
-// more than its highest child's): every edge child -> parent of a height
-// folds the finished child row into its parent together with the child's
-// coupling terms, D_p += k_{p,n} - k_{p,n} k_{n,p}/D_n and R_p += k_{p,n}
-// R_n/D_n - k_{p,n} (v_p - v_n).  A height's records are sorted by parent,
-// and the thread at the head of each parent's run folds the run in order
-// and adds the total to the parent once, so no row is written by two
-// threads in a phase and the result does not depend on scheduling.  Back-substitution walks the same
-// heights downwards from the root: dv_n = (R_n + k_{n,p} dv_p)/D_n.  Each
-// height is one barrier.  The coupling coefficients are precomputed per
-// record at mech_bind_cable, and a unit's records are staged in LDS once, so
-// a height waits on LDS alone.
+// A unit's rows and records sit in LDS.  What bounds the solve is the chain of
+// dependent rounds and the memory latencies before and after them, not bytes:
+// a round is one LDS read, a reciprocal, an LDS write and a barrier, about
+// 0.2 us.  Rounds with no more records than a wave has lanes are run by one
+// wave without workgroup barriers.
 //
-// A workgroup solves one unit with its rows and edge records in LDS (44 B
-// per position); a FULL unit holds one or more whole cells.  A cell too large for LDS is cut: every maximal subtree that fits becomes a
-// piece (small pieces share a unit as a forest), and the rest, the trunk,
-// one TOP unit.  Pieces eliminate up to their roots and hand the rows over
-// in global memory; the trunk's unit takes each piece root's row as a ghost
-// leaf, solves, and hands back the root's dv; the pieces then
-// back-substitute, and so do whole cells, whose elimination ran beside the
-// pieces'.  The elimination order within each tree stays a valid
-// Hines order, so the result is the same elimination up to rounding.  A
-// trunk larger than LDS is solved with its rows in global memory, accessed
-// at device scope.
-template <bool LDS> __device__ __forceinline__ double ldc(const double *p) {
-    if constexpr (LDS) return *p;
-    else return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A cell larger than a unit takes two launches.  In the first, pieces
+// eliminate up to their roots and the trunk's rows are assembled (the only
+// reads of other units' v).  In the second, every piece solves its cell's
+// trunk again for itself, with the piece roots' rows as ghost leaves (a
+// trunk of a cell cut at 1024 nodes has at most a few hundred rows, and
+// solving it in each piece takes a launch less than solving it once), then
+// walks its own rounds backwards; the cell's first piece also writes the
+// trunk's v.  Trunks that do not fit beside a piece take a launch of their
+// own in between, in LDS or, if they are larger than that, with their rows
+// in global memory.
+//
+// Solve of 64 cells of 200 to 20 000 compartments (369 k in all): 36 us a step,
+// where elimination by heights in three launches took 88; of 6 cells of 200 to
+// 2000 (5.8 k): 15 us, where it took 48.
+// A row: S, T, U and N side by side, 32 bytes.
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f64x2 row_st(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i); }
+__device__ __forceinline__ f64x2 row_un(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i + 2); }
+__device__ __forceinline__ void set_st(double *rows, int i, double s, double t) {
+    *(f64x2 *)(rows + 4 * (size_t)i) = f64x2{s, t};
 }
-template <bool LDS> __device__ __forceinline__ void stc(double *p, double v) {
-    if constexpr (LDS) *p = v;
-    else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void set_un(double *rows, int i, double u, double n) {
+    *(f64x2 *)(rows + 4 * (size_t)i + 2) = f64x2{u, n};
 }
-// A single addition to a row that no other thread touches in this phase:
-// issued as an atomic so that the thread need not wait for the row's value.
-template <bool LDS> __device__ __forceinline__ void addc(double *p, double v) {
-    if constexpr (LDS) atomicAdd(p, v);
-    else __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-constexpr int kCableLevelsLds = 1024;   // level boundaries staged in LDS
-constexpr int kBatch = 4;               // loop iterations whose loads are issued together
+enum { kS = 0, kT = 1, kU = 2, kN = 3 };
+__device__ __forceinline__ double &row_at(double *rows, int i, int k) { return rows[4 * (size_t)i + k]; }
+struct TreeRecs {
+    const char *children, *more, *fold, *elim;
+    const int *rf, *re;
+    int nr;
+};
+constexpr int kBatch = 2;   // loop iterations whose loads are issued together
+// What the first kBatch rows of a thread keep from the assembly for the
+// voltage update.
+struct TreeKeep {
+    int n[kBatch], src[kBatch];
+    double v[kBatch];
+};
 
 // Workgroup barrier for phases that share data only through LDS: it waits
-// for LDS traffic alone, so global loads issued before it (the next level's
-// records) stay in flight across it.  The global-scratch variant needs the
-// full barrier, whose fence also drains global memory operations.
-template <bool LDS> __device__ __forceinline__ void level_barrier() {
+// for LDS traffic alone, so global loads issued before it stay in flight
+// across it.  Rows in global memory need the full barrier, whose fence also
+// orders global memory operations within the workgroup.
+template <bool LDS> __device__ __forceinline__ void tree_barrier() {
     if constexpr (LDS) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
@@ -862,279 +873,521 @@ template <bool LDS> __device__ __forceinline__ void level_barrier() {
         __syncthreads();
     }
 }
+// Orders one wave's own LDS accesses (the hardware keeps their order; the
+// compiler must not move them).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-template <bool LDS>
-__global__ __launch_bounds__(512) void k_cable(CableDev c, NodesDev nd, GlobDev g, const int *units, int down) {
-    extern __shared__ double lds[];
-    __shared__ int lvl[kCableLevelsLds + 1];
-    const int tid = (int)threadIdx.x, B = (int)blockDim.x;
-    const int u = units[blockIdx.x];
-    const int p0 = c.unit_pos[u], p1 = c.unit_pos[u + 1], np = p1 - p0;
-    const int mode = c.unit_mode[u];
-    const int L0 = c.unit_elim[u], L1 = c.unit_elim[u + 1], nlev = L1 - L0;
-    const int e0 = c.elim_ptr[L0], ne = c.elim_ptr[L1] - e0;
-    // Rows: in LDS at position - p0, in global memory at the position.
-    // Records (index q - e0): in LDS the unit's records, staged once, with
-    // both row indices and the run length packed into one int (a unit in
-    // LDS has at most kCableLdsUnitMax rows).
-    const int base = LDS ? p0 : 0;
-    double *D = LDS ? lds : c.D;
-    double *R = LDS ? lds + np : c.R;
-    double *DV = LDS ? lds + 2 * np : c.DV;
-    double *ekn = LDS ? lds + 3 * np : c.ekn + e0;
-    double *ekp = LDS ? lds + 3 * np + ne : c.ekp + e0;
-    int *rec = (int *)(lds + 3 * np + 2 * ne);
-    const bool lv_lds = nlev < kCableLevelsLds;
-    if (lv_lds)
-        for (int j = tid; j <= nlev; j += B) lvl[j] = c.elim_ptr[L0 + j] - e0;
-    auto lv = [&](int j) { return lv_lds ? lvl[j] : c.elim_ptr[L0 + j] - e0; };
-    // Passes over a unit's positions or records take kBatch iterations at a
-    // time and issue all their global loads before using any, so a pass
-    // waits about n / (kBatch B) memory latencies instead of n / B.
-    if constexpr (LDS)
-        for (int q0 = tid; q0 < ne; q0 += kBatch * B) {
-            int a[kBatch], b[kBatch], l[kBatch];
-            double x[kBatch], y[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int q = q0 + k * B;
-                if (q < ne) {
-                    a[k] = c.elim_n[e0 + q];
-                    b[k] = c.elim_p[e0 + q];
-                    l[k] = c.elim_run[e0 + q];
-                    x[k] = c.ekn[e0 + q];
-                    y[k] = c.ekp[e0 + q];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int q = q0 + k * B;
-                if (q < ne) {
-                    rec[q] = (a[k] - p0) | ((b[k] - p0) << 12) | (l[k] << 24);
-                    ekn[q] = x[k];
-                    ekp[q] = y[k];
-                }
-            }
-        }
-    auto rows = [&](int q, int &rn, int &rp) {
-        if constexpr (LDS) {
-            const unsigned r = (unsigned)rec[q];
-            rn = (int)(r & 0xfffu);
-            rp = (int)((r >> 12) & 0xfffu);
-        } else {
-            rn = c.elim_n[e0 + q];
-            rp = c.elim_p[e0 + q];
-        }
-    };
-    auto run_of = [&](int q) {
-        if constexpr (LDS) return (int)((unsigned)rec[q] >> 24);
-        else return c.elim_run[e0 + q];
-    };
+// Copies `bytes` (a multiple of 16, both ends aligned to 16) into LDS without
+// passing through registers: nothing waits for the copy before tree_copied().
+__device__ __forceinline__ void tree_copy(char *dst, const void *src, int bytes) {
+    const int lane = (int)(threadIdx.x & 63), step = (int)(blockDim.x >> 6) * 1024;
+    for (int o = uni((int)(threadIdx.x >> 6)) * 1024; o < bytes; o += step)
+        if (o + 16 * lane < bytes)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)((const char *)src + o + 16 * lane),
+                (__attribute__((address_space(3))) void *)(dst + o), 16, 0, 0);
+}
+// This wave's copies are in LDS (a barrier makes all waves' so).
+__device__ __forceinline__ void tree_copied() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-    if (!down) {
-        // rows: every position writes its own terms (ghosts bring the piece
-        // root's eliminated row instead) and its voltage difference to the
-        // parent, which its parent's fold needs
-        for (int i0 = p0 + tid; i0 < p1; i0 += kBatch * B) {
-            int n[kBatch], p[kBatch], src[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int i = i0 + k * B;
-                if (i < p1) {
-                    n[k] = c.pos_node[i];
-                    p[k] = c.pos_pnode[i];
-                    src[k] = c.pos_src[i];
-                }
-            }
-            double vn[kBatch], vp[kBatch], a[kBatch], b[kBatch], e[kBatch], f[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int i = i0 + k * B;
-                if (i < p1) {
-                    vn[k] = nd.v[n[k]];
-                    vp[k] = p[k] >= 0 ? nd.v[p[k]] : vn[k];
-                    if (src[k] >= 0) {
-                        a[k] = c.D[src[k]];
-                        b[k] = c.R[src[k]];
-                    } else {
-                        a[k] = nd.cm[n[k]];
-                        b[k] = nd.rhs[n[k]];
-                        e[k] = nd.d[n[k]];
-                        f[k] = c.kn[n[k]];
-                    }
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int i = i0 + k * B;
-                if (i < p1) {
-                    const double dv = p[k] >= 0 ? vp[k] - vn[k] : 0.0;
-                    double Dn = a[k], Rn = b[k];
-                    if (src[k] < 0) {
-                        Dn = 1e-3 * a[k] / g.dt + e[k] + f[k];
-                        Rn = b[k] + f[k] * dv;
-                    }
-                    stc<LDS>(D + (i - base), Dn);
-                    stc<LDS>(R + (i - base), Rn);
-                    stc<LDS>(DV + (i - base), dv);
-                }
-            }
-        }
-        __syncthreads();
+// A unit's tables at `at`, which stands for the block's byte `from`.
+__device__ __forceinline__ TreeRecs tree_recs(const TreeUnit &u, const char *at, int from) {
+    const char *b = at - from;
+    return TreeRecs{b, b + u.o_more, b + u.o_fold, b + u.o_elim, (const int *)(b + u.o_rf), (const int *)(b + u.o_re), u.nr};
+}
+// Bytes of a unit's rows in LDS: its own and the one that stands for a missing
+// neighbour.
+__device__ __forceinline__ int tree_bytes(int np) { return 32 * (np + 1); }
+__device__ __forceinline__ double *tree_rows(char *lds, int np) {
+    double *rows = (double *)lds;
+    if (threadIdx.x == 0) {
+        set_st(rows, np, 1.0, 0.0);
+        set_un(rows, np, 0.0, 0.0);
+    }
+    return rows;
+}
 
-        // leaves to root, one height per barrier.  The top height of a FULL
-        // or TOP unit holds its roots' records (a root paired with itself,
-        // couplings 0), which serve the back-substitution alone.
-        const int nel = mode == kUnitPiece ? nlev : nlev - 1;
-        for (int j = 0; j < nel; ++j) {
-            const int qlo = lv(j), qend = lv(j + 1);
-            for (int q = qlo + tid; q < qend; q += B) {
-                int rn, rp;
-                rows(q, rn, rp);
-                const int run = run_of(q);
-                // the first child's row is read before the run is looked at,
-                // so a run of one (nearly all) costs no more than a scatter
-                const double Dn = ldc<LDS>(D + rn), Rn = ldc<LDS>(R + rn), dvn = ldc<LDS>(DV + rn);
-                const double kp = ekp[q], kn0 = ekn[q];
-                if (run == 0) continue;   // folded by the head of its parent's run
-                const double f = fdiv(kp, Dn);
-                double aD = kp - f * kn0, aR = f * Rn - kp * dvn;
-                if (run != 1) {
-                    // further children of the parent at this height, in order; a
-                    // run of kCableRunMax goes on while the parent matches
-                    const int end = run < kCableRunMax ? q + run : qend;
-                    for (int r = q + 1; r < end; ++r) {
-                        int cn, cp;
-                        rows(r, cn, cp);
-                        if (cp != rp) break;
-                        const double Dc = ldc<LDS>(D + cn), Rc = ldc<LDS>(R + cn), dvc = ldc<LDS>(DV + cn);
-                        const double kq = ekp[r], h = fdiv(kq, Dc);
-                        aD += kq - h * ekn[r];
-                        aR += h * Rc - kq * dvc;
-                    }
-                }
-                // the parent's only addition of this height
-                addc<LDS>(D + rp, aD);
-                addc<LDS>(R + rp, aR);
-            }
-            level_barrier<LDS>();
-        }
-        if (mode != kUnitTop) {
-            // eliminated rows go to the second pass (and a piece root's to its
-            // trunk's unit): whole cells back-substitute there too, beside the
-            // pieces, which keeps this pass as short as the longest elimination
-            if constexpr (LDS)
-                for (int i = p0 + tid; i < p1; i += B) {
-                    c.D[i] = D[i - base];
-                    c.R[i] = R[i - base];
-                }
-            return;
-        }
+// Next row of a list; `m` becomes -1 at its end.
+template <bool LDS> __device__ __forceinline__ int more_row(const TreeRecs &rc, int &m) {
+    if constexpr (LDS) {
+        const unsigned x = ((const unsigned short *)rc.more)[m];
+        m = (x & 0x8000u) ? -1 : m + 1;
+        return (int)(x & 0xfffu);
     } else {
-        // second pass of a piece or whole cells: the eliminated rows, and at
-        // each piece root the dv its trunk's unit handed back
-        if constexpr (LDS)
-            for (int i0 = p0 + tid; i0 < p1; i0 += kBatch * B) {
-                double x[kBatch], y[kBatch];
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const int i = i0 + k * B;
-                    if (i < p1) {
-                        x[k] = c.D[i];
-                        y[k] = c.R[i];
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const int i = i0 + k * B;
-                    if (i < p1) {
-                        D[i - base] = x[k];
-                        R[i - base] = y[k];
-                    }
-                }
-            }
-        __syncthreads();
+        const unsigned x = ((const unsigned *)rc.more)[m];
+        m = (x & kMoreLast) ? -1 : m + 1;
+        return (int)(x & ~kMoreLast);
     }
+}
+// First child of a row and the list of the others, -1 without.
+template <bool LDS> __device__ __forceinline__ void children_of(const TreeRecs &rc, int i, int &ch, int &m) {
+    if constexpr (LDS) {
+        const unsigned x = ((const unsigned *)rc.children)[i];
+        ch = (int)(x & 0xfff);
+        if (ch == kNoRow) ch = -1;
+        m = (x >> 12) == kChildNone ? -1 : (int)(x >> 12);
+    } else {
+        const int2 x = ((const int2 *)rc.children)[i];
+        ch = x.x;
+        m = x.y;
+    }
+}
 
-    // root to leaves: dv overwrites R.  The records in reverse height order
-    // visit every parent before its children; a root's own record gives
-    // dv = R/D.
-    for (int j = nlev - 1; j >= 0; --j) {
-        const int qend = lv(j + 1);
-        for (int q = lv(j) + tid; q < qend; q += B) {
-            int rn, rp;
-            rows(q, rn, rp);
-            const double r = ldc<LDS>(R + rn) + ekn[q] * ldc<LDS>(R + rp);
-            stc<LDS>(R + rn, fdiv(r, ldc<LDS>(D + rn)));
-        }
-        level_barrier<LDS>();
+// Folds the eliminated neighbours of one surviving row.  N of an eliminated
+// row is written by its child's thread and read by nobody before the walk
+// back.  All neighbours are read before any is used: the chain through a round
+// is one LDS read, one reciprocal and one LDS write.
+__device__ __forceinline__ void fold_packed(double *r, const TreeRecs &rc, unsigned long long w, int np) {
+    const int t = (int)(w & 0xfff), p = (int)((w >> 12) & 0xfff), c = (int)((w >> 24) & 0xfff);
+    const int d = (int)((w >> 36) & 0xfff);
+    int m = (int)(w >> 48) == (int)kMoreNone ? -1 : (int)(w >> 48);
+    const f64x2 st = row_st(r, t), sc = row_st(r, c), sd = row_st(r, d), sp = row_st(r, p);
+    const double ut = row_at(r, t, kU), uc = row_at(r, c, kU), ud = row_at(r, d, kU), up = row_at(r, p, kU);
+    const bool has = p != np;
+    const double u = has ? ut : 0.0;
+    const double fc = uc * rcp_d(sc.x), fd = ud * rcp_d(sd.x), fp = u * rcp_d(sp.x);
+    double S = fma(-u, fp, fma(-ud, fd, fma(-uc, fc, st.x)));
+    double T = fma(fp, sp.y, fma(fd, sd.y, fma(fc, sc.y, st.y)));
+    while (m >= 0) {
+        const int i = more_row<true>(rc, m);
+        const f64x2 si = row_st(r, i);
+        const double ui = row_at(r, i, kU), f = ui * rcp_d(si.x);
+        S = fma(-ui, f, S);
+        T = fma(f, si.y, T);
     }
-    for (int i0 = p0 + tid; i0 < p1; i0 += kBatch * B) {
-        int n[kBatch], src[kBatch];
-        double v0[kBatch];
+    set_st(r, t, S, T);
+    row_at(r, t, kU) = has ? fp * up : ut;
+    row_at(r, p, kN) = ut;   // without a parent: the row that stands for it, whose N nobody reads
+}
+__device__ __forceinline__ void fold_wide(double *r, const TreeRecs &rc, int q) {
+    const int4 w = ((const int4 *)rc.fold)[q];
+    const int t = w.x, p = w.y;
+    const f64x2 st = row_st(r, t);
+    double S = st.x, T = st.y;
+    auto child = [&](int i) {
+        const f64x2 si = row_st(r, i);
+        const double u = row_at(r, i, kU), f = u * rcp_d(si.x);
+        S = fma(-u, f, S);
+        T = fma(f, si.y, T);
+    };
+    if (w.z >= 0) child(w.z);
+    for (int m = w.w; m >= 0;) child(more_row<false>(rc, m));
+    if (p >= 0) {
+        const f64x2 sp = row_st(r, p);
+        const double u = row_at(r, t, kU), f = u * rcp_d(sp.x);
+        S = fma(-u, f, S);
+        T = fma(f, sp.y, T);
+        row_at(r, p, kN) = u;
+        row_at(r, t, kU) = f * row_at(r, p, kU);
+    }
+    set_st(r, t, S, T);
+}
+
+// The boundaries of a unit's rounds, one per lane of every wave (a unit in LDS
+// has fewer than 64 rounds), so that a round reads them without a trip to LDS.
+__device__ __forceinline__ int tree_bounds(const int *at, int nr) { return at[min((int)(threadIdx.x & 63), nr)]; }
+__device__ __forceinline__ int bound_at(int b, int j) { return __builtin_amdgcn_readlane(b, j); }
+
+// All rounds of a unit.  In LDS the next round's record is read before the
+// barrier, so that it is there when the round starts.
+template <bool LDS> __device__ __forceinline__ void tree_up(double *r, const TreeRecs &rc, int np) {
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x;
+    if constexpr (LDS) {
+        const unsigned long long *rec = (const unsigned long long *)rc.fold;
+        const int bnd = tree_bounds(rc.rf, rc.nr), last = bound_at(bnd, rc.nr);
+        auto rounds = [&](int j, int stride, auto done, auto sync) {
+            int lo = bound_at(bnd, j), q = lo + tid;
+            unsigned long long w = rec[min(q, last - 1)];
+            for (; !done(j); ++j) {
+                const int hi = bound_at(bnd, j + 1);
+                const unsigned long long next = rec[min(hi + tid, last - 1)];
+                if (q < hi) fold_packed(r, rc, w, np);
+                for (q += stride; q < hi; q += stride) fold_packed(r, rc, rec[q], np);
+                sync();
+                q = hi + tid;
+                w = next;
+            }
+            return j;
+        };
+        int j = 0;
+        if (rc.nr > 0) {
+            auto tail = [&](int i) {
+                return i == rc.nr || bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave;
+            };
+            j = rounds(0, B, tail, [] { tree_barrier<true>(); });
+            if (tid < 64 && j < rc.nr) rounds(j, 64, [&](int i) { return i == rc.nr; }, [] { wave_order(); });
+        }
+        tree_barrier<true>();
+    } else {
+        for (int j = 0; j < rc.nr; ++j) {
+            const int hi = uni(rc.rf[j + 1]);
+            for (int q = uni(rc.rf[j]) + tid; q < hi; q += B) fold_wide(r, rc, q);
+            tree_barrier<false>();
+        }
+    }
+}
+
+// T, U and N become T/S, U/S and N/S.
+__device__ __forceinline__ void tree_quotient(const double *from, double *to, int i) {
+    const f64x2 st = row_st(from, i), un = row_un(from, i);
+    const double f = rcp_d(st.x);
+    set_st(to, i, st.x, fdiv(st.y, st.x));
+    set_un(to, i, un.x * f, un.y * f);
+}
+template <bool LDS> __device__ __forceinline__ void tree_quotients(double *r, int n) {
+    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) tree_quotient(r, r, i);
+    tree_barrier<LDS>();
+}
+
+// The rounds backwards: dv of the eliminated rows, in T, from the rows that
+// outlived them.  What a round reads of its own rows does not change any more
+// and is read a round ahead, its record two rounds ahead: after a barrier only
+// the neighbours' dv are read.
+template <bool LDS> __device__ __forceinline__ void tree_down(double *r, const TreeRecs &rc) {
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x;
+    if constexpr (LDS) {
+        if (rc.nr == 0) return;
+        const unsigned long long *rec = (const unsigned long long *)rc.elim;
+        const int bnd = tree_bounds(rc.re, rc.nr), last = bound_at(bnd, rc.nr);
+        struct Row {
+            int i, p, c;
+            double x, u, n;
+        };
+        auto word = [&](int j) { return rec[min(bound_at(bnd, max(j, 0)) + tid, last - 1)]; };
+        auto load = [&](unsigned long long w) {
+            Row s;
+            s.i = (int)(w & 0xfff);
+            s.p = (int)((w >> 12) & 0xfff);
+            s.c = (int)((w >> 24) & 0xfff);
+            const f64x2 un = row_un(r, s.i);
+            s.x = row_at(r, s.i, kT);
+            s.u = un.x;
+            s.n = un.y;
+            return s;
+        };
+        auto one = [&](const Row &s) {
+            row_at(r, s.i, kT) = fma(s.n, row_at(r, s.c, kT), fma(s.u, row_at(r, s.p, kT), s.x));
+        };
+        auto rounds = [&](int j, int stride, auto done, auto sync) {
+            unsigned long long w1 = word(j - 1);
+            Row row = load(word(j));
+            for (; !done(j); --j) {
+                const int lo = bound_at(bnd, j), hi = bound_at(bnd, j + 1);
+                const unsigned long long w2 = word(j - 2);
+                const Row next = load(w1);
+                if (lo + tid < hi) one(row);
+                for (int q = lo + tid + stride; q < hi; q += stride) one(load(rec[q]));
+                sync();
+                row = next;
+                w1 = w2;
+            }
+            return j;
+        };
+        auto small = [&](int i) { return bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave; };
+        int j = rc.nr - 1;
+        if (tid < 64) rounds(j, 64, [&](int i) { return i < 0 || !small(i); }, [] { wave_order(); });
+        while (j >= 0 && small(j)) --j;
+        tree_barrier<true>();
+        if (j >= 0) rounds(j, B, [](int i) { return i < 0; }, [] { tree_barrier<true>(); });
+    } else {
+        for (int j = rc.nr - 1; j >= 0; --j) {
+            const int hi = uni(rc.re[j + 1]);
+            for (int q = uni(rc.re[j]) + tid; q < hi; q += B) {
+                const int4 w = ((const int4 *)rc.elim)[q];
+                const f64x2 un = row_un(r, w.x);
+                double x = fma(un.x, row_at(r, w.y, kT), row_at(r, w.x, kT));
+                if (w.z != w.x) x = fma(un.y, row_at(r, w.z, kT), x);
+                row_at(r, w.x, kT) = x;
+            }
+            tree_barrier<false>();
+        }
+    }
+}
+
+// The rows of a unit from this step's v, rhs, d and cm; ghosts (TAKE) bring
+// the rows that their pieces handed over.  A row's currents to its children
+// come from the children's rows, which leave them in N.
+template <bool LDS, bool TAKE>
+__device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev &nd, const GlobDev &g, double *r,
+                                              const TreeRecs &rc, int p0, int np, TreeKeep &keep) {
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x;
+    for (int i0 = tid; i0 < np; i0 += kBatch * B) {
+        int4 w[kBatch];
+        double a[kBatch], gu[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int i = i0 + k * B;
-            if (i < p1) {
-                n[k] = c.pos_node[i];
-                src[k] = c.pos_src[i];
+            if (i < np) {
+                w[k] = c.pos[p0 + i];
+                a[k] = c.pa[p0 + i];
+                gu[k] = c.pu[p0 + i];
             }
         }
+        double v[kBatch], vp[kBatch], x[kBatch], y[kBatch], cm[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+            if (i0 + k * B < np) {
+                const int n = w[k].x;
+                v[k] = nd.v[n];
+                vp[k] = nd.v[w[k].y >= 0 ? w[k].y : n];
+                if (TAKE && w[k].z >= 0) {
+                    const f64x2 st = row_st(c.G, w[k].z);
+                    y[k] = st.x;
+                    x[k] = st.y;
+                } else {
+                    x[k] = nd.rhs[n];
+                    y[k] = nd.d[n];
+                }
+                cm[k] = nd.cm[n];
+            }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int i = i0 + k * B;
-            if (i < p1 && src[k] < 0) v0[k] = nd.v[n[k]];
+            if (i < np) {
+                const double f = gu[k] * (vp[k] - v[k]);
+                const bool ghost = TAKE && w[k].z >= 0;
+                set_st(r, i, ghost ? y[k] : fma(a[k], 1e-3 * cm[k] / g.dt + y[k], gu[k]),
+                       ghost ? x[k] : fma(a[k], x[k], f));
+                set_un(r, i, gu[k], w[k].w == -1 ? f : 0.0);
+                if (i0 == tid) {
+                    keep.n[k] = w[k].x;
+                    keep.src[k] = w[k].z;
+                    keep.v[k] = v[k];
+                }
+            }
+        }
+    }
+    tree_copied();
+    tree_barrier<LDS>();
+    for (int i = tid; i < np; i += B) {
+        int ch, m;
+        children_of<LDS>(rc, i, ch, m);
+        if (ch < 0) continue;
+        f64x2 st = row_st(r, i);
+        for (;;) {
+            const f64x2 un = row_un(r, ch);
+            st.x += un.x;
+            st.y -= un.y;
+            row_at(r, ch, kN) = 0.0;
+            if (m < 0) break;
+            ch = more_row<LDS>(rc, m);
+        }
+        set_st(r, i, st.x, st.y);
+    }
+    tree_barrier<LDS>();
+}
+
+// v of the unit's own nodes from dv in T, and spikes; ghosts hand dv to the
+// piece's root (HAND).  `r` are the unit's rows, `keep` holds the first rows' nodes and v, which are
+// all rows unless the unit has more than kBatch per thread.
+template <bool HAND>
+__device__ __forceinline__ void tree_voltage(const CableDev &c, const NodesDev &nd, const GlobDev &g, double *r,
+                                             int p0, int np, TreeKeep &keep) {
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x;
+    for (int i0 = tid; i0 < np; i0 += kBatch * B) {
+        if (i0 != tid) {
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k)
+                if (i0 + k * B < np) {
+                    const int4 w = c.pos[p0 + i0 + k * B];
+                    keep.n[k] = w.x;
+                    keep.src[k] = w.z;
+                    keep.v[k] = nd.v[w.x];
+                }
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             const int i = i0 + k * B;
-            if (i >= p1) continue;
-            const double dv = ldc<LDS>(R + (i - base));
-            if (src[k] >= 0) {
-                c.R[src[k]] = dv;   // the piece root's dv, for its second pass
+            if (i >= np) continue;
+            const double dv = row_at(r, i, kT), v0 = keep.v[k];
+            if (keep.src[k] >= 0) {
+                if (HAND) row_at(c.G, keep.src[k], kT) = dv;
                 continue;
             }
-            const double v1 = v0[k] + dv;
-            if (v0[k] < g.vthresh && v1 >= g.vthresh) nd.spikes[n[k]] += 1;
-            nd.v[n[k]] = v1;
+            const double v1 = v0 + dv;
+            if (v0 < g.vthresh && v1 >= g.vthresh) nd.spikes[keep.n[k]] += 1;
+            nd.v[keep.n[k]] = v1;
         }
     }
+}
+
+// First launch: whole cells to the end; pieces up to their roots; the rows of
+// trunks that pieces solve.
+__global__ __launch_bounds__(1024) void k_tree_a(CableDev c, NodesDev nd, GlobDev g) {
+    extern __shared__ __align__(16) char tree_lds[];
+    const TreeUnit u = c.units_a[blockIdx.x];
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x, p0 = u.p0, np = u.np;
+    double *r = tree_rows(tree_lds, np);
+    char *tab = tree_lds + tree_bytes(np);
+    tree_copy(tab, c.block + 16 * (size_t)u.block,
+              u.mode == kUnitFull ? u.bytes : u.mode == kUnitPiece ? u.o_re : u.o_fold);
+    const TreeRecs rc = tree_recs(u, tab, 0);
+    TreeKeep keep;
+    tree_assemble<true, false>(c, nd, g, r, rc, p0, np, keep);
+    double *out = c.G + 4 * (size_t)p0;
+    if (u.mode == kUnitTop) {
+        for (int i = tid; i < np; i += B) {
+            const f64x2 st = row_st(r, i);
+            set_st(out, i, st.x, st.y);
+        }
+        return;
+    }
+    tree_up<true>(r, rc, np);
+    if (u.mode == kUnitPiece) {
+        // a root's row stays as it is, for its trunk
+        for (int i = tid; i < np; i += B) {
+            tree_quotient(r, out, i);
+            if (c.pos[p0 + i].w != -1) row_at(out, i, kT) = row_at(r, i, kT);
+        }
+        return;
+    }
+    tree_quotients<true>(r, np);
+    tree_down<true>(r, rc);
+    tree_voltage<false>(c, nd, g, r, p0, np, keep);
+}
+
+// A trunk on its own.
+template <bool LDS>
+__global__ __launch_bounds__(1024) void k_tree_top(CableDev c, NodesDev nd, GlobDev g, const TreeUnit *units) {
+    extern __shared__ __align__(16) char tree_lds[];
+    const TreeUnit u = units[blockIdx.x];
+    const char *block = c.block + 16 * (size_t)u.block;
+    double *r;
+    TreeRecs rc;
+    if constexpr (LDS) {
+        r = tree_rows(tree_lds, u.np);
+        char *tab = tree_lds + tree_bytes(u.np);
+        tree_copy(tab, block, u.bytes);
+        rc = tree_recs(u, tab, 0);
+    } else {
+        r = c.G + 4 * (size_t)u.p0;
+        rc = tree_recs(u, block, 0);
+    }
+    TreeKeep keep;
+    tree_assemble<LDS, true>(c, nd, g, r, rc, u.p0, u.np, keep);
+    tree_up<LDS>(r, rc, u.np);
+    tree_quotients<LDS>(r, u.np);
+    tree_down<LDS>(r, rc);
+    tree_voltage<true>(c, nd, g, r, u.p0, u.np, keep);
+}
+
+// Last launch: a piece's rows from its roots' dv, which come from the trunk
+// solved here or in its own launch; and v of the trunks solved here.
+__global__ __launch_bounds__(1024) void k_tree_b(CableDev c, NodesDev nd, GlobDev g) {
+    extern __shared__ __align__(16) char tree_lds[];
+    const TreeUnit u = c.units_b[2 * blockIdx.x], t = c.units_b[2 * blockIdx.x + 1];
+    const int tid = (int)threadIdx.x, B = (int)blockDim.x, p0 = u.p0, np = u.np;
+    const bool piece = u.mode == kUnitPiece, trunk = !piece || u.solves_trunk;
+    // first rows' nodes, v and (a root's) ghost row
+    TreeKeep keep;
+    int ghost[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+        const int i = tid + k * B;
+        if (i < np) {
+            const int4 w = c.pos[p0 + i];
+            keep.n[k] = w.x;
+            keep.src[k] = w.z;
+            ghost[k] = w.w;
+        }
+    }
+    char *at = tree_lds;
+    double *x = (double *)at;   // the piece's rows
+    TreeRecs rp{};
+    if (piece) {
+        tree_copy(at, c.G + 4 * (size_t)p0, 32 * np);
+        at += tree_bytes(np);
+        tree_copy(at, c.block + 16 * (size_t)u.block + u.o_re, u.bytes - u.o_re);
+        rp = tree_recs(u, at, u.o_re);
+        at += u.bytes - u.o_re;
+    }
+    double *r = nullptr;   // the trunk's
+    if (trunk) {
+        const int nt = t.np;
+        r = tree_rows(at, nt);
+        char *tab = at + tree_bytes(nt);
+        tree_copy(tab, c.block + 16 * (size_t)t.block, t.bytes);
+        const TreeRecs rc = tree_recs(t, tab, 0);
+        for (int i = tid; i < nt; i += B) {
+            const int src = c.pos[t.p0 + i].z;
+            const f64x2 st = row_st(c.G, src >= 0 ? src : t.p0 + i);
+            set_st(r, i, st.x, st.y);
+            set_un(r, i, c.pu[t.p0 + i], 0.0);
+        }
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+            if (tid + k * B < np) keep.v[k] = nd.v[keep.n[k]];
+        tree_copied();
+        tree_barrier<true>();
+        tree_up<true>(r, rc, nt);
+        tree_quotients<true>(r, nt);
+        tree_down<true>(r, rc);
+        if (!piece) {
+            tree_voltage<false>(c, nd, g, r, p0, nt, keep);
+            return;
+        }
+        for (int i0 = tid; i0 < np; i0 += kBatch * B) {
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k) {
+                const int i = i0 + k * B;
+                if (i >= np) continue;
+                const int gr = i0 == tid ? ghost[k] : c.pos[p0 + i].w;
+                if (gr >= 0) row_at(x, i, kT) = row_at(r, gr, kT);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+            if (tid + k * B < np) keep.v[k] = nd.v[keep.n[k]];
+        tree_copied();
+    }
+    if (tid == 0) row_at(x, np, kT) = 0.0;   // the missing child of a leaf
+    tree_barrier<true>();
+    tree_down<true>(x, rp);
+    tree_voltage<false>(c, nd, g, x, p0, np, keep);
 }
 
 hipError_t launch_cable(const CableDev &c, const NodesDev &nd, const GlobDev &g, hipStream_t s) {
-    const size_t lds = kCableLdsBytesPerNode * (size_t)c.lds_max_nodes;
-    if (c.n_up > 0) k_cable<true><<<c.n_up, 512, lds, s>>>(c, nd, g, c.list_up, 0);
-    if (c.n_top > 0) k_cable<true><<<c.n_top, 512, lds, s>>>(c, nd, g, c.list_top, 0);
-    if (c.n_top_g > 0) k_cable<false><<<c.n_top_g, 512, 0, s>>>(c, nd, g, c.list_top_g, 0);
-    if (c.n_down > 0) k_cable<true><<<c.n_down, 512, lds, s>>>(c, nd, g, c.list_down, 1);
+    if (c.n_a > 0) k_tree_a<<<c.n_a, c.block_a, c.lds_a, s>>>(c, nd, g);
+    if (c.n_top > 0) k_tree_top<true><<<c.n_top, c.block_a, c.lds_top, s>>>(c, nd, g, c.units_top);
+    if (c.n_top_g > 0) k_tree_top<false><<<c.n_top_g, 1024, 0, s>>>(c, nd, g, c.units_top_g);
+    if (c.n_b > 0) k_tree_b<<<c.n_b, c.block_b, c.lds_b, s>>>(c, nd, g);
     return hipGetLastError();
 }
 
-// Coupling coefficients of the tree from the bound area and g_axial: per node
-// (towards its parent) and per edge record (the node's towards its parent and
-// the parent's towards it; 0 for a root's own record).
-__global__ void k_cable_coeffs(CableDev c, const double *area, int n_nodes, int n_edges) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_nodes) {
-        const int p = c.parent[i];
-        c.kn[i] = p >= 0 ? 1e2 * c.g_axial[i] / area[i] : 0.0;
-    }
-    if (i < n_edges) {
-        const int n = c.pos_node[c.elim_n[i]], p = c.parent[n];
-        const double ga = c.g_axial[n];
-        c.ekn[i] = p >= 0 ? 1e2 * ga / area[n] : 0.0;
-        c.ekp[i] = p >= 0 ? 1e2 * ga / area[p] : 0.0;
+// Per position, from the bound area and g_axial: the conductance to the parent
+// and area/100 (1 at a node without edges, whose row needs no scaling: its step
+// is then the isolated update's to the last rounding).
+__global__ __launch_bounds__(256) void k_cable_coeffs(CableDev c, const double *area) {
+    const TreeUnit u = c.units[blockIdx.x];
+    const TreeRecs rc = tree_recs(u, c.block + 16 * (size_t)u.block, 0);
+    for (int i = (int)threadIdx.x; i < u.np; i += (int)blockDim.x) {
+        const int p = u.p0 + i, n = c.pos[p].x;
+        const double gu = c.parent[n] >= 0 ? c.g_axial[n] : 0.0;
+        int ch, m;
+        if (u.wide) children_of<false>(rc, i, ch, m);
+        else children_of<true>(rc, i, ch, m);
+        c.pu[p] = gu;
+        c.pa[p] = ch < 0 && c.parent[n] < 0 ? 1.0 : area[n] * 1e-2;
     }
 }
 
-hipError_t launch_cable_coeffs(const CableDev &c, const double *area, int n_nodes, int n_edges, hipStream_t s) {
-    const int n = n_nodes > n_edges ? n_nodes : n_edges;
-    if (n > 0) k_cable_coeffs<<<(n + 255) / 256, 256, 0, s>>>(c, area, n_nodes, n_edges);
+hipError_t launch_cable_coeffs(const CableDev &c, const double *area, hipStream_t s) {
+    if (c.n_units > 0) k_cable_coeffs<<<c.n_units, 256, 0, s>>>(c, area);
     return hipGetLastError();
 }
 
 hipError_t cable_allow_lds(size_t bytes) {
-    return hipFuncSetAttribute((const void *)k_cable<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    const void *fns[] = {(const void *)k_tree_a, (const void *)k_tree_top<true>, (const void *)k_tree_b};
+    for (const void *f : fns) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ---------------------------------------------------------- fused path --

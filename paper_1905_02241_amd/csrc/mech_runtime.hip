@@ -89,229 +89,49 @@ struct SlotHost {
     bool has_gid = false, has_ica = false;
 };
 
-// Cell trees of the cable mode, cut into units on the host at
-// mech_bind_cable (the unit kinds and positions are described with CableDev).
-struct CableHost {
-    std::vector<int32_t> parent, pos_node, pos_par, pos_src, elim_n, elim_p, elim_ptr, unit_pos, unit_elim,
-        unit_mode, list_up, list_top, list_top_g, list_down, pos_pnode, elim_run;
-    int lds_max = 0;
+// The device buffer of the cell trees: offsets of its arrays, sized from the
+// cut alone.
+enum {
+    kCabParent, kCabPos, kCabUnits, kCabUnitsA, kCabUnitsTop, kCabUnitsTopG, kCabUnitsB, kCabBlock, kCabUploaded,
+    kCabPa = kCabUploaded, kCabPu, kCabG, kCabArrays
 };
-
-// Validates Hines order and contiguous cells, then cuts the trees into units
-// of at most `cap` positions (a trunk may exceed it) and writes each unit's
-// edge records bucketed by the child's height.  Returns "" on success.
-std::string build_cable(int64_t N, const int32_t *parent, int cap, CableHost &h) {
-    h = CableHost();
-    if (cap < 1) cap = 1;
-    std::vector<int32_t> first;
-    for (int64_t n = 0; n < N; ++n) {
-        const int32_t p = parent[n];
-        if (p < -1 || p >= n) return "parent[n] must be -1 or a node index below n (Hines order)";
-        if (p < 0) first.push_back((int32_t)n);
-        else if (first.empty() || p < first.back())
-            return "every cell must be a contiguous node range starting at its root";
-    }
-    if (N > 0 && (first.empty() || first[0] != 0)) return "node 0 must be a root";
-    const int n_cells = (int)first.size();
-    first.push_back((int32_t)N);
-    h.parent.assign(parent, parent + N);
-    std::vector<int32_t> sub(N, 1), ht(N, 0);
-    for (int64_t n = N - 1; n >= 0; --n)
-        if (parent[n] >= 0) {
-            sub[parent[n]] += sub[n];
-            ht[parent[n]] = std::max(ht[parent[n]], ht[n] + 1);
-        }
-    std::vector<int32_t> pos(N, -1), th(N, 0), levels;
-    h.unit_pos.push_back(0);
-    h.elim_ptr.push_back(0);
-    struct Rec { int32_t h, n, p; };
-    // closes the unit whose positions were placed last; recs are (height,
-    // child position, parent position), a root paired with itself
-    auto add_unit = [&](int mode, std::vector<Rec> &recs, int nlev) {
-        const int u = (int)h.unit_mode.size();
-        h.unit_mode.push_back(mode);
-        h.unit_pos.push_back((int32_t)h.pos_node.size());
-        h.unit_elim.push_back((int32_t)h.elim_ptr.size() - 1);
-        // by height, and within a height by parent, so that a parent's
-        // children of one height form a run that one thread folds in order
-        std::stable_sort(recs.begin(), recs.end(),
-                         [](const Rec &x, const Rec &y) { return x.h != y.h ? x.h < y.h : x.p < y.p; });
-        size_t k = 0;
-        for (int L = 0; L < nlev; ++L) {
-            for (; k < recs.size() && recs[k].h == L; ++k) {
-                h.elim_n.push_back(recs[k].n);
-                h.elim_p.push_back(recs[k].p);
-                // the head of a parent's run of this height carries the run's
-                // length (at most kCableRunMax, longer runs are followed by
-                // parent); the others 0
-                int run = 0;
-                if (k == 0 || recs[k - 1].h != L || recs[k - 1].p != recs[k].p)
-                    while (k + run < recs.size() && recs[k + run].h == L && recs[k + run].p == recs[k].p &&
-                           run < kCableRunMax)
-                        ++run;
-                h.elim_run.push_back(run);
-            }
-            h.elim_ptr.push_back((int32_t)h.elim_n.size());
-        }
-        levels.push_back(nlev);
-        const int size = h.unit_pos[u + 1] - h.unit_pos[u];
-        if (mode != kUnitTop || size <= cap) h.lds_max = std::max(h.lds_max, size);
-        if (mode == kUnitFull || mode == kUnitPiece) h.list_up.push_back(u);
-        if (mode == kUnitFull || mode == kUnitPiece) h.list_down.push_back(u);
-        if (mode == kUnitTop) (size <= cap ? h.list_top : h.list_top_g).push_back(u);
-    };
-    auto place = [&](int32_t n, int32_t par_pos, int32_t src) {
-        const int32_t i = (int32_t)h.pos_node.size();
-        h.pos_node.push_back(n);
-        h.pos_pnode.push_back(parent[n]);
-        h.pos_par.push_back(par_pos);
-        h.pos_src.push_back(src);
-        return i;
-    };
-
-    // whole cells that fit, packed into forests of up to `pack` nodes so that
-    // many small cells do not each take a workgroup
-    int64_t fit_nodes = 0;
-    for (int c = 0; c < n_cells; ++c)
-        if (first[c + 1] - first[c] <= cap) fit_nodes += first[c + 1] - first[c];
-    const int pack = (int)std::min<int64_t>(cap, std::max<int64_t>(1024, (fit_nodes + 511) / 512));
-    std::vector<Rec> recs;
-    int nlev = 0, cur = 0;
-    auto close_full = [&]() {
-        // every root's own record goes to the unit's top height
-        for (Rec &r : recs)
-            if (r.h < 0) r.h = nlev - 1;
-        if (cur > 0) add_unit(kUnitFull, recs, nlev);
-        recs.clear();
-        nlev = 0;
-        cur = 0;
-    };
-    for (int c = 0; c < n_cells; ++c) {
-        const int32_t a = first[c], b = first[c + 1];
-        if (b - a > cap) continue;
-        if (cur + (b - a) > pack) close_full();
-        for (int32_t n = a; n < b; ++n) {
-            const int32_t p = parent[n];
-            pos[n] = place(n, p >= 0 ? pos[p] : -1, -1);
-            recs.push_back({p >= 0 ? ht[n] : -1, pos[n], p >= 0 ? pos[p] : pos[n]});
-        }
-        nlev = std::max(nlev, ht[a] + 1);
-        cur += b - a;
-    }
-    close_full();
-
-    // cells too large: maximal subtrees that fit become pieces, packed into
-    // forests; the trunk (subtree larger than cap) is one unit
-    for (int c = 0; c < n_cells; ++c) {
-        const int32_t a = first[c], b = first[c + 1];
-        if (b - a <= cap) continue;
-        std::vector<int32_t> pid(b - a, -1), roots, unit_of;
-        std::vector<int> piece_unit_size;
-        for (int32_t n = a; n < b; ++n) {
-            if (sub[n] > cap) continue;
-            const int32_t p = parent[n];
-            if (sub[p] > cap) {
-                pid[n - a] = (int32_t)roots.size();
-                roots.push_back(n);
-            } else {
-                pid[n - a] = pid[p - a];
-            }
-        }
-        // greedy packing in root order
-        int units = 0, fill = 0;
-        for (int32_t r : roots) {
-            if (units == 0 || fill + sub[r] > cap) {
-                ++units;
-                fill = 0;
-            }
-            fill += sub[r];
-            unit_of.push_back(units - 1);
-        }
-        std::vector<std::vector<int32_t>> members(units);
-        for (int32_t n = a; n < b; ++n)
-            if (pid[n - a] >= 0) members[unit_of[pid[n - a]]].push_back(n);
-        for (int k = 0; k < units; ++k) {
-            recs.clear();
-            int nl = 0;
-            for (int32_t n : members[k]) {
-                const int32_t p = parent[n];
-                const bool root = sub[p] > cap;
-                pos[n] = place(n, root ? -1 : pos[p], -1);
-                if (root) nl = std::max(nl, ht[n]);
-                else recs.push_back({ht[n], pos[n], pos[p]});
-            }
-            add_unit(kUnitPiece, recs, nl);
-        }
-        // the trunk with the piece roots as ghost leaves; heights counted
-        // within the unit (a ghost is a leaf)
-        std::vector<int32_t> tn;
-        for (int32_t n = a; n < b; ++n)
-            if (sub[n] > cap || (parent[n] >= 0 && sub[parent[n]] > cap)) tn.push_back(n);
-        for (auto it = tn.rbegin(); it != tn.rend(); ++it) th[*it] = 0;
-        for (auto it = tn.rbegin(); it != tn.rend(); ++it)
-            if (parent[*it] >= 0) th[parent[*it]] = std::max(th[parent[*it]], th[*it] + 1);
-        recs.clear();
-        for (size_t k = 0; k < tn.size(); ++k) {
-            const int32_t n = tn[k], p = parent[n];
-            const bool ghost = sub[n] <= cap;
-            const int32_t i = place(n, p >= 0 ? pos[p] : -1, ghost ? pos[n] : -1);
-            if (!ghost) pos[n] = i;   // trunk nodes: their only position
-            recs.push_back({th[n], i, p >= 0 ? pos[p] : i});
-        }
-        add_unit(kUnitTop, recs, th[a] + 1);
-    }
-    h.unit_elim.push_back((int32_t)h.elim_ptr.size() - 1);
-    // tallest units first so that the longest chains of barriers start first
-    auto by_height = [&](std::vector<int32_t> &l) {
-        std::stable_sort(l.begin(), l.end(), [&](int32_t x, int32_t y) { return levels[x] > levels[y]; });
-    };
-    by_height(h.list_up);
-    by_height(h.list_top);
-    by_height(h.list_top_g);
-    by_height(h.list_down);
-    return "";
-}
-
-// Device layout of a CableHost (256-byte aligned arrays), then the double
-// arrays: ekn, ekp (per edge record), D, R (per position), kn (per node), DV
-// (per position).
-constexpr int kCableIntArrays = 16;
 size_t cable_layout(const CableHost &h, int64_t N, size_t *offs) {
-    const std::vector<int32_t> *arr[kCableIntArrays] = {
-        &h.parent, &h.pos_node, &h.pos_par, &h.pos_src, &h.elim_n, &h.elim_p, &h.elim_ptr,
-        &h.unit_pos, &h.unit_elim, &h.unit_mode, &h.list_up, &h.list_top, &h.list_top_g, &h.list_down,
-        &h.pos_pnode, &h.elim_run};
+    const size_t P = h.pos_node.size(), U = h.unit_mode.size();
+    const std::vector<char> wide = wide_units(h);
+    size_t bytes[kCabArrays];
+    bytes[kCabParent] = 4 * (size_t)N;
+    bytes[kCabPos] = 16 * P;
+    for (int j : {kCabUnits, kCabUnitsA, kCabUnitsTop, kCabUnitsTopG}) bytes[j] = sizeof(TreeUnit) * U;
+    bytes[kCabUnitsB] = 2 * sizeof(TreeUnit) * U;
+    bytes[kCabBlock] = 0;
+    for (size_t u = 0; u < U; ++u)
+        bytes[kCabBlock] += table_bound((size_t)(h.unit_pos[u + 1] - h.unit_pos[u]), wide[u]);
+    bytes[kCabPa] = bytes[kCabPu] = 8 * P;
+    bytes[kCabG] = 32 * P;
     size_t off = 0;
-    auto take = [&](size_t bytes) {
-        const size_t o = off;
-        off = (off + std::max<size_t>(bytes, 8) + kAlign - 1) / kAlign * kAlign;
-        return o;
-    };
-    for (int j = 0; j < kCableIntArrays; ++j) offs[j] = take(4 * arr[j]->size());
-    const size_t E = h.elim_n.size(), P = h.pos_node.size(), NN = (size_t)std::max<int64_t>(N, 1);
-    offs[kCableIntArrays + 0] = take(8 * E);    // ekn
-    offs[kCableIntArrays + 1] = take(8 * E);    // ekp
-    offs[kCableIntArrays + 2] = take(8 * P);    // D
-    offs[kCableIntArrays + 3] = take(8 * P);    // R
-    offs[kCableIntArrays + 4] = take(8 * NN);   // kn
-    offs[kCableIntArrays + 5] = take(8 * P);    // DV
+    for (int j = 0; j < kCabArrays; ++j) {
+        offs[j] = off;
+        off = (off + std::max<size_t>(bytes[j], 8) + kAlign - 1) / kAlign * kAlign;
+    }
     return off;
 }
 
-// Positions of a unit whose rows and records fit the LDS a workgroup may
-// take on the current device (at most kCableLdsUnitMax, for the packed
-// records).
-int cable_lds_nodes() {
+// Dynamic LDS the cable kernels may take on the current device.
+int cable_lds_bytes() {
     int dev = 0, bytes = 65536;
     if (hipGetDevice(&dev) == hipSuccess) {
         int b = 0;
         if (hipDeviceGetAttribute(&b, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && b > 0)
             bytes = b;
     }
-    // the level-boundary table of k_cable takes 4 KiB of static LDS; a unit's
-    // packed records hold 12-bit rows
-    return std::min(kCableLdsUnitMax, std::max(0, (bytes - 8192) / kCableLdsBytesPerNode));
+    return std::max(0, bytes - 8192);
 }
+// Positions of a unit whose rows and records fit that LDS (at most
+// kCableLdsUnitMax, for the packed records).
+int cable_fit_nodes(int lds_bytes) {
+    return std::max(1, std::min(kCableLdsUnitMax, (lds_bytes - kCableLdsFixed) / kCableLdsBytesPerNode));
+}
+int cable_lds_nodes() { return cable_fit_nodes(cable_lds_bytes()); }
 
 struct Layout {
     size_t total = 0;
@@ -1069,24 +889,36 @@ int mech_bind_nodes(mech_ctx *c, double *v, double *rhs, double *d, const double
 
 // The unit size bound for a requested unit_nodes, at most the device's LDS
 // capacity; the fallback capacity is the one without the large-LDS opt-in.
-// The default, 1024 nodes, was the fastest bound on branched cells of 200 to
-// 20 000 compartments (units of 512 to 4096 nodes measured): smaller units
-// run more workgroups at once, larger ones leave fewer trunk heights.
-constexpr int kCableFallbackNodes = (65536 - 8192) / kCableLdsBytesPerNode;
+// The default keeps cells whole where every cell fits LDS, which makes the
+// solve one launch, and cuts at 1024 nodes where one does not (a second launch
+// is then needed anyway, and units of 512 to 2048 nodes solve within 2 % of
+// each other).  Solve of 1000 cells of 1300 compartments: 44 us whole, 82 cut
+// at 1024; 200 of 2000: 20 and 32; 6 of 200 to 2000: 15.1 and 20.5.
+constexpr int kCableFallbackBytes = 65536 - 8192;
 constexpr int kCableDefaultUnit = 1024;
-int cable_cap(int32_t unit_nodes, int lds_nodes) {
-    return std::min<int>(unit_nodes > 0 ? unit_nodes : kCableDefaultUnit, lds_nodes);
+int cable_cap(int64_t n_nodes, const int32_t *parent, int32_t unit_nodes, int lds_nodes) {
+    if (unit_nodes > 0) return std::min<int>(unit_nodes, lds_nodes);
+    int64_t largest = 0, first = 0;
+    for (int64_t n = 1; n <= n_nodes; ++n)
+        if (n == n_nodes || parent[n] < 0) {
+            largest = std::max(largest, n - first);
+            first = n;
+        }
+    return std::min<int>(largest <= lds_nodes ? (int)std::max<int64_t>(largest, kCableDefaultUnit) : kCableDefaultUnit,
+                         lds_nodes);
 }
 
 int mech_cable_required_bytes(int64_t n_nodes, const int32_t *parent, int32_t unit_nodes, size_t *out) {
     if (!out || n_nodes < 0 || (n_nodes > 0 && !parent) || unit_nodes < 0)
         return fail(nullptr, MECH_ERR_INVAL, "null argument or negative unit_nodes");
-    size_t need = 0, offs[kCableIntArrays + 6];
+    size_t need = 0, offs[kCabArrays];
     // mech_bind_cable cuts with the device's capacity, or with the fallback
     // if the device refuses the large LDS request: size for both
-    for (int lds : {std::max(cable_lds_nodes(), 1), kCableFallbackNodes}) {
+    const int caps[2] = {cable_cap(n_nodes, parent, unit_nodes, cable_lds_nodes()),
+                         cable_cap(n_nodes, parent, unit_nodes, cable_fit_nodes(kCableFallbackBytes))};
+    for (int j = 0; j < (caps[0] == caps[1] ? 1 : 2); ++j) {
         CableHost h;
-        std::string why = build_cable(n_nodes, parent, cable_cap(unit_nodes, lds), h);
+        std::string why = build_cable(n_nodes, parent, caps[j], h, false);
         if (!why.empty()) return fail(nullptr, MECH_ERR_INVAL, "%s", why.c_str());
         need = std::max(need, cable_layout(h, n_nodes, offs));
     }
@@ -1099,7 +931,7 @@ int mech_cable_plan(int64_t n_nodes, const int32_t *parent, int32_t unit_nodes, 
     if (!sizes || n_nodes < 0 || (n_nodes > 0 && !parent) || unit_nodes < 0 || buf_len < 0)
         return fail(nullptr, MECH_ERR_INVAL, "null argument or negative size");
     CableHost h;
-    std::string why = build_cable(n_nodes, parent, cable_cap(unit_nodes, std::max(cable_lds_nodes(), 1)), h);
+    std::string why = build_cable(n_nodes, parent, cable_cap(n_nodes, parent, unit_nodes, cable_lds_nodes()), h, true);
     if (!why.empty()) return fail(nullptr, MECH_ERR_INVAL, "%s", why.c_str());
     constexpr int kPlanArrays = 14;   // pos_pnode (parent of pos_node) is not part of the plan
     const std::vector<int32_t> *arr[kPlanArrays] = {
@@ -1123,60 +955,142 @@ int mech_bind_cable(mech_ctx *c, const int32_t *parent, const double *g_axial, i
         return fail(c, MECH_ERR_INVAL, "parent, g_axial and dev_buf are required");
     if (unit_nodes < 0) return fail(c, MECH_ERR_INVAL, "unit_nodes must be >= 0");
     if (((uintptr_t)dev_buf % kAlign) != 0) return fail(c, MECH_ERR_INVAL, "dev_buf must be %d-byte aligned", kAlign);
-    int lds_nodes = std::max(cable_lds_nodes(), 1);
-    if (lds_nodes * kCableLdsBytesPerNode > 65536 &&
-        cable_allow_lds((size_t)lds_nodes * kCableLdsBytesPerNode) != hipSuccess) {
+    int lds_bytes = cable_lds_bytes();
+    if (lds_bytes > kCableFallbackBytes && cable_allow_lds((size_t)lds_bytes) != hipSuccess) {
         (void)hipGetLastError();
-        lds_nodes = kCableFallbackNodes;
+        lds_bytes = kCableFallbackBytes;
     }
     CableHost h;
-    std::string why = build_cable(c->n_nodes, parent, cable_cap(unit_nodes, lds_nodes), h);
+    std::string why = build_cable(c->n_nodes, parent, cable_cap(c->n_nodes, parent, unit_nodes, cable_fit_nodes(lds_bytes)), h, false);
     if (!why.empty()) return fail(c, MECH_ERR_INVAL, "%s", why.c_str());
-    size_t offs[kCableIntArrays + 6];
+    size_t offs[kCabArrays];
     const size_t need = cable_layout(h, c->n_nodes, offs);
     if (dev_bytes < need) return fail(c, MECH_ERR_NOMEM, "cable buffer has %zu bytes, %zu required", dev_bytes, need);
+    TreeTables t;
+    {
+        TreeSchedule s;
+        build_schedule(h, s);
+        tree_tables(h, s, t);
+    }
+    // Trunks that every piece of the cell has room for beside its own rows
+    // are solved by the pieces; the others take a launch of their own.
+    const int U = (int)t.unit.size();
+    auto row_bytes = [](const TreeUnit &u) { return 32 * ((size_t)u.np + 1); };
+    auto trunk_bytes = [&](const TreeUnit &u) { return row_bytes(u) + (size_t)u.bytes; };
+    auto piece_bytes = [&](const TreeUnit &u) { return row_bytes(u) + (size_t)(u.bytes - u.o_re); };
+    std::vector<int> trunk_of;
+    std::vector<size_t> piece_max;
+    for (int u = 0; u < U; ++u) {
+        if (t.unit[u].nr > (t.unit[u].wide ? kTreeRounds : 63))
+            return fail(c, MECH_ERR_STATE, "internal: %d elimination rounds in a unit", t.unit[u].nr);
+        if (h.cell_of[u] < 0) continue;
+        const size_t cell = (size_t)h.cell_of[u];
+        if (trunk_of.size() <= cell) {
+            trunk_of.resize(cell + 1, -1);
+            piece_max.resize(cell + 1, 0);
+        }
+        if (t.unit[u].mode == kUnitTop) trunk_of[cell] = u;
+        else piece_max[cell] = std::max(piece_max[cell], piece_bytes(t.unit[u]));
+    }
+    std::vector<char> shared(U, 0);
+    std::vector<TreeUnit> ua, ut, ug, ub;
+    size_t lds_a = 0, lds_top = 0, lds_b = 0, rows_a = 0, rows_b = 0;
+    for (int32_t u : h.list_top)
+        shared[u] = trunk_bytes(t.unit[u]) + piece_max[h.cell_of[u]] <= (size_t)lds_bytes;
+    for (int32_t u : h.list_up) {
+        TreeUnit &x = t.unit[u];
+        if (x.mode == kUnitPiece) x.solves_trunk = shared[trunk_of[h.cell_of[u]]];
+        ua.push_back(x);
+        lds_a = std::max(lds_a, row_bytes(x) + (size_t)(x.mode == kUnitFull ? x.bytes : x.o_re));
+        rows_a = std::max(rows_a, (size_t)x.np);
+    }
+    for (int32_t u : h.list_down) {
+        const TreeUnit &x = t.unit[u];
+        if (x.mode != kUnitPiece) continue;
+        const TreeUnit &y = t.unit[trunk_of[h.cell_of[u]]];
+        ub.push_back(x);
+        ub.push_back(y);
+        lds_b = std::max(lds_b, piece_bytes(x) + (x.solves_trunk ? trunk_bytes(y) : 0));
+        rows_b = std::max(rows_b, (size_t)x.np);
+    }
+    for (int32_t u : h.list_top) {
+        const TreeUnit &x = t.unit[u];
+        rows_a = std::max(rows_a, (size_t)x.np);
+        if (shared[u]) {
+            ua.push_back(x);
+            lds_a = std::max(lds_a, row_bytes(x) + (size_t)x.o_fold);
+            ub.push_back(x);
+            ub.push_back(x);
+            lds_b = std::max(lds_b, trunk_bytes(x));
+            rows_b = std::max(rows_b, (size_t)x.np);
+        } else {
+            ut.push_back(x);
+            lds_top = std::max(lds_top, trunk_bytes(x));
+        }
+    }
+    for (int32_t u : h.list_top_g) ug.push_back(t.unit[u]);
+    std::vector<int32_t> pos(4 * h.pos_node.size());
+    for (int u = 0; u < U; ++u)
+        for (int p = h.unit_pos[u]; p < h.unit_pos[u + 1]; ++p) {
+            pos[4 * (size_t)p] = h.pos_node[p];
+            pos[4 * (size_t)p + 1] = h.pos_pnode[p];
+            pos[4 * (size_t)p + 2] = -1;
+            pos[4 * (size_t)p + 3] = h.pos_par[p] >= 0 ? -1 : -2;
+        }
+    for (int u = 0; u < U; ++u)
+        for (int p = h.unit_pos[u]; p < h.unit_pos[u + 1]; ++p)
+            if (const int src = h.pos_src[p]; src >= 0) {
+                pos[4 * (size_t)p + 2] = src;
+                if (shared[u]) pos[4 * (size_t)src + 3] = p - h.unit_pos[u];
+            }
+    // one upload of everything but the double arrays
+    std::vector<char> img(offs[kCabUploaded]);
+    bool fits = true;
+    auto put = [&](int j, const void *p, size_t bytes) {
+        if (offs[j] + bytes > offs[j + 1]) fits = false;
+        else if (bytes) memcpy(img.data() + offs[j], p, bytes);
+    };
+    put(kCabParent, h.parent.data(), 4 * h.parent.size());
+    put(kCabPos, pos.data(), 4 * pos.size());
+    put(kCabUnits, t.unit.data(), sizeof(TreeUnit) * t.unit.size());
+    put(kCabUnitsA, ua.data(), sizeof(TreeUnit) * ua.size());
+    put(kCabUnitsTop, ut.data(), sizeof(TreeUnit) * ut.size());
+    put(kCabUnitsTopG, ug.data(), sizeof(TreeUnit) * ug.size());
+    put(kCabUnitsB, ub.data(), sizeof(TreeUnit) * ub.size());
+    put(kCabBlock, t.block.data(), t.block.size());
+    if (!fits) return fail(c, MECH_ERR_STATE, "internal: a cable array exceeds its bound");
     char *b = (char *)dev_buf;
-    const std::vector<int32_t> *arr[kCableIntArrays] = {
-        &h.parent, &h.pos_node, &h.pos_par, &h.pos_src, &h.elim_n, &h.elim_p, &h.elim_ptr,
-        &h.unit_pos, &h.unit_elim, &h.unit_mode, &h.list_up, &h.list_top, &h.list_top_g, &h.list_down,
-        &h.pos_pnode, &h.elim_run};
-    for (int j = 0; j < kCableIntArrays; ++j)
-        if (!arr[j]->empty())
-            HIPCHK(c, hipMemcpy(b + offs[j], arr[j]->data(), 4 * arr[j]->size(), hipMemcpyHostToDevice));
-    const int *I[kCableIntArrays];
-    for (int j = 0; j < kCableIntArrays; ++j) I[j] = (const int *)(b + offs[j]);
+    if (!img.empty() && c->n_nodes > 0) HIPCHK(c, hipMemcpy(b, img.data(), img.size(), hipMemcpyHostToDevice));
+    auto units = [&](int j) { return (const TreeUnit *)(b + offs[j]); };
+    auto D = [&](int j) { return (double *)(b + offs[j]); };
     CableDev d{};
     d.g_axial = g_axial;
-    d.parent = I[0];
-    d.pos_node = I[1];
-    d.pos_par = I[2];
-    d.pos_src = I[3];
-    d.elim_n = I[4];
-    d.elim_p = I[5];
-    d.elim_ptr = I[6];
-    d.unit_pos = I[7];
-    d.unit_elim = I[8];
-    d.unit_mode = I[9];
-    d.list_up = I[10];
-    d.list_top = I[11];
-    d.list_top_g = I[12];
-    d.list_down = I[13];
-    d.pos_pnode = I[14];
-    d.elim_run = I[15];
-    d.n_up = (int)h.list_up.size();
-    d.n_top = (int)h.list_top.size();
-    d.n_top_g = (int)h.list_top_g.size();
-    d.n_down = (int)h.list_down.size();
-    d.lds_max_nodes = h.lds_max;
-    d.ekn = (double *)(b + offs[kCableIntArrays + 0]);
-    d.ekp = (double *)(b + offs[kCableIntArrays + 1]);
-    d.D = (double *)(b + offs[kCableIntArrays + 2]);
-    d.R = (double *)(b + offs[kCableIntArrays + 3]);
-    d.kn = (double *)(b + offs[kCableIntArrays + 4]);
-    d.DV = (double *)(b + offs[kCableIntArrays + 5]);
+    d.parent = (const int *)(b + offs[kCabParent]);
+    d.pos = (const int4 *)(b + offs[kCabPos]);
+    d.units = units(kCabUnits);
+    d.units_a = units(kCabUnitsA);
+    d.units_top = units(kCabUnitsTop);
+    d.units_top_g = units(kCabUnitsTopG);
+    d.units_b = units(kCabUnitsB);
+    d.block = b + offs[kCabBlock];
+    d.n_units = U;
+    d.n_a = (int)ua.size();
+    d.n_top = (int)ut.size();
+    d.n_top_g = (int)ug.size();
+    d.n_b = (int)ub.size() / 2;
+    d.lds_a = (int)lds_a;
+    d.lds_top = (int)lds_top;
+    d.lds_b = (int)lds_b;
+    // a thread for every two rows of the largest unit
+    auto block = [](size_t rows) { return (int)std::min<size_t>(1024, std::max<size_t>(64, (rows / 2 + 63) / 64 * 64)); };
+    d.block_a = block(rows_a);
+    d.block_b = block(rows_b);
+    d.pa = D(kCabPa);
+    d.pu = D(kCabPu);
+    d.G = D(kCabG);
     if (c->n_nodes > 0) {
         if (!c->nd.area) return fail(c, MECH_ERR_STATE, "bind area (mech_bind_nodes) before mech_bind_cable");
-        HIPCHK(c, launch_cable_coeffs(d, c->nd.area, (int)c->n_nodes, (int)h.elim_n.size(), c->stream));
+        HIPCHK(c, launch_cable_coeffs(d, c->nd.area, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     }
     c->cable = d;

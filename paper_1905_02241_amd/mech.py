@@ -196,7 +196,7 @@ class Mechanisms:
     def bind_cable(self, parent, g_axial, unit_nodes: int = 0):
         """Cell trees for the cable mode: parent (-1 at roots, Hines order,
         contiguous cells) and axial conductances in uS.  unit_nodes bounds
-        the subtree one workgroup solves (0: the device's LDS capacity)."""
+        the subtree one workgroup solves (0: the library's default)."""
         par = np.ascontiguousarray(parent, dtype=np.int32)
         nbytes = C.c_size_t(0)
         ip = C.POINTER(C.c_int32)
@@ -384,7 +384,7 @@ def cable_plan(parent, unit_nodes: int = 0) -> Dict[str, np.ndarray]:
 def from_workload(w, prec: str = "fp64", init: bool = True, unit_nodes: int = 0, static: bool = False) -> Mechanisms:
     """Build a context from a workload (paper_1905_02241_amd.workloads):
     node index, parameters, globals, node arrays (and cell trees, cut into
-    units of at most unit_nodes, 0 for the device's capacity); v = v_init
+    units of at most unit_nodes, 0 for the library's default); v = v_init
     everywhere and, if `init`, every STATE at its steady state there.
     static: the context lives in the library's static device area
     (mech_alloc_static)."""
