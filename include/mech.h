@@ -301,8 +301,10 @@ int mech_step(mech_ctx *ctx, int64_t nsteps, int64_t k0, double dt, int vmode, i
  * MECH_LAUNCH_NONTEMPORAL: instance arrays streamed with the non-temporal
  * hint, as they are touched once per step; MECH_LAUNCH_PLAIN_ATOMIC: the
  * PLAIN path's current update scatters one FP64 atomic per instance instead
- * of the wave-segmented per-node sum, for comparison).  Rebuilds
- * the tile table.  BATCHED and RESIDENT results do not depend on the shape
+ * of the wave-segmented per-node sum, for comparison).  Until the first call
+ * the batched path takes a shape for the context's size and the time-fused path
+ * 256 threads with tiles of 2048 instances and 1024 nodes.  Rebuilds the tile
+ * table.  BATCHED and RESIDENT results do not depend on the shape
  * (their node sums are order-independent); PLAIN's rhs/d differ from one
  * run to the next by the rounding order of its atomics.                    */
 enum { MECH_LAUNCH_XCD_ORDER = 1, MECH_LAUNCH_NONTEMPORAL = 2, MECH_LAUNCH_PLAIN_ATOMIC = 4 };

@@ -183,6 +183,14 @@ void compute_layout(int64_t n_nodes, std::vector<SlotHost> &slots, int prec, Lay
     L.total = off;
 }
 
+// A launch shape of the fused paths and its tile table.
+struct Launch {
+    int block = 256, budget = 2048, nodes = 1024, blocks_per_cu = 0, flags = MECH_LAUNCH_XCD_ORDER;
+    int64_t n_tiles = 0, max_nodes = 0;
+    size_t first = 0;                 // first row in the device's table region
+    std::vector<int32_t> rows;        // host copy of the tile table
+};
+
 }  // namespace
 
 struct mech_ctx {
@@ -194,15 +202,18 @@ struct mech_ctx {
     hipStream_t stream = nullptr;
     hipStream_t capture_stream = nullptr;
     std::vector<SlotHost> slots;
+    std::vector<int32_t> per_node;   // instances of all types on each node
     Layout L;
     Globals gl;
     NodesDev nd{};
     CableDev cable{};
     bool nodes_bound = false, clamp_bound = false, has_syn = false, cable_bound = false;
-    // fused-path launch shape and tile table
-    int block = 256, tile_budget = 2048, tile_nodes = 1024, blocks_per_cu = 0, launch_flags = MECH_LAUNCH_XCD_ORDER;
-    int64_t n_tiles = 0, max_tile_nodes = 0;
-    std::vector<int32_t> tile_rows;   // host copy of the tile table
+    // Launch shape and tile table of the time-fused path, and of the batched
+    // path once the caller has chosen a shape; until then the batched path
+    // takes `fit`, the shape for the context's size.
+    Launch set, fit;
+    bool chosen = false;
+    const Launch &batched() const { return chosen ? set : fit; }
     int n_cu = 256;
     // time-fused path: steps per launch, and the dynamic LDS its kernels may take
     int res_steps = 64;
@@ -327,52 +338,71 @@ SlotDev slot_dev(const mech_ctx *c, int s) {
     return d;
 }
 
-int build_tiles(mech_ctx *c) {
-    const int ns = (int)c->slots.size();
-    const int row = 1 + ns;
-    std::vector<int32_t> rows;
+// The tile table of a launch shape: tiles are closed by the instances on each
+// node alone, and a tile's first instance of a type is the first one on or
+// after its first node (instances are sorted by node).
+void make_tiles(const mech_ctx *c, Launch &l) {
+    std::vector<int32_t> &rows = l.rows;
+    rows.clear();
     rows.reserve(1024);
-    std::vector<int64_t> ptr(ns, 0);
     auto push = [&](int64_t node) {
         rows.push_back((int32_t)node);
-        for (int s = 0; s < ns; ++s) rows.push_back((int32_t)ptr[s]);
+        for (const SlotHost &h : c->slots)
+            rows.push_back(h.identity ? (int32_t)node
+                                      : (int32_t)(std::lower_bound(h.ni.begin(), h.ni.end(), (int32_t)node) - h.ni.begin()));
     };
     push(0);
     int64_t cost = 0, nodes = 0, max_nodes = 0;
-    int64_t nxt[kMaxSlots];
     for (int64_t n = 0; n < c->n_nodes; ++n) {
-        int64_t cn = 0;
-        for (int s = 0; s < ns; ++s) {
-            const auto &ni = c->slots[s].ni;
-            nxt[s] = ptr[s];
-            while (nxt[s] < (int64_t)ni.size() && ni[nxt[s]] == n) ++nxt[s];
-            cn += nxt[s] - ptr[s];
-        }
-        if (nodes > 0 && (cost + cn > c->tile_budget || nodes >= c->tile_nodes)) {
+        const int64_t cn = c->per_node[n];
+        if (nodes > 0 && (cost + cn > l.budget || nodes >= l.nodes)) {
             push(n);
             max_nodes = std::max(max_nodes, nodes);
             cost = 0;
             nodes = 0;
         }
-        for (int s = 0; s < ns; ++s) ptr[s] = nxt[s];
         cost += cn;
         ++nodes;
     }
     max_nodes = std::max(max_nodes, nodes);
     push(c->n_nodes);
-    const int64_t nrows = (int64_t)rows.size() / row;
-    if (nrows > c->L.max_tile_rows)
-        return fail(c, MECH_ERR_NOMEM, "tile table needs %lld rows, room for %lld", (long long)nrows,
+    l.n_tiles = c->n_nodes > 0 ? (int64_t)rows.size() / (1 + (int64_t)c->slots.size()) - 1 : 0;
+    l.max_nodes = max_nodes;
+}
+
+// Uploads the shape's tile table behind the first `first` rows.
+int upload_tiles(mech_ctx *c, Launch &l, size_t first) {
+    const size_t row = 1 + c->slots.size(), nrows = l.rows.size() / row;
+    if (first + nrows > (size_t)c->L.max_tile_rows)
+        return fail(c, MECH_ERR_NOMEM, "tile table needs %zu rows, room for %lld", first + nrows,
                     (long long)c->L.max_tile_rows);
-    c->n_tiles = c->n_nodes > 0 ? nrows - 1 : 0;
-    c->max_tile_nodes = max_nodes;
-    HIPCHK(c, hipMemcpyAsync(c->buf + c->L.off_tiles, rows.data(), rows.size() * 4, hipMemcpyHostToDevice,
-                             c->stream));
+    l.first = first;
+    HIPCHK(c, hipMemcpyAsync(c->buf + c->L.off_tiles + 4 * row * first, l.rows.data(), l.rows.size() * 4,
+                             hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    c->tile_rows = std::move(rows);
     c->res_lds_cache.clear();
     clear_graphs(c);
     return MECH_OK;
+}
+
+// The batched path's shape for a context whose caller has not chosen one:
+// 256 threads, and tiles that keep every CU busy and grow with the work, so
+// that a thread takes one instance where latency counts and eight where
+// streaming does.  A tile spans at most 640 nodes (30 KiB of LDS, five
+// workgroups a CU).  us per step at this tile / at the default's 2048
+// instances, by instances per CU (256 of them):
+//     39 (hh)      5.6 / 12.0      1291 (cells, five types) 13.8 / 17.2
+//     391 (hh)     7.4 / 12.8      3908 (C5's mix)          23.2 / 26.6
+//     781 (hh+pas) 7.9 / 14.1      7813 (hh+pas, 640 nodes) 33.6 / 37.8
+// and at 5988 (cells) 2048 instances 27.4, 1024 29.2.
+Launch fit_launch(const mech_ctx *c) {
+    Launch l;
+    int64_t total = 0;
+    for (const auto &h : c->slots) total += h.n;
+    const int64_t w = total / c->n_cu;
+    l.budget = w < 512 ? 256 : w < 2048 ? 512 : w < 5000 ? 1024 : 2048;
+    l.nodes = std::min(l.budget, 640);
+    return l;
 }
 
 // Reject a step with unbound inputs before anything is enqueued.
@@ -438,7 +468,7 @@ int launch_plain_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int a
     a.err = (int *)(c->buf + c->L.off_err);
     a.g = g;
     a.nd = c->nd;
-    a.atomic_scatter = (c->launch_flags & MECH_LAUNCH_PLAIN_ATOMIC) ? 1 : 0;
+    a.atomic_scatter = (c->set.flags & MECH_LAUNCH_PLAIN_ATOMIC) ? 1 : 0;
     if (cur && !accumulate) HIPCHK(c, launch_fill(c->nd.rhs, c->nd.d, (int)c->n_nodes, c->stream));
     if (cur && !accumulate && g.shared_ca) HIPCHK(c, launch_fill(c->nd.ica, c->nd.ica, (int)c->n_nodes, c->stream));
     for (int s = 0; s < (int)c->slots.size(); ++s) {
@@ -454,28 +484,28 @@ int launch_plain_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int a
     return MECH_OK;
 }
 
-FusedArgs fused_args(mech_ctx *c, const GlobDev &g, int kofs) {
+FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int kofs) {
     FusedArgs a{};
     for (int s = 0; s < (int)c->slots.size(); ++s) a.slot[s] = slot_dev(c, s);
     a.n_slots = (int)c->slots.size();
     a.has_syn = c->has_syn ? 1 : 0;
     for (const auto &h : c->slots) a.has_ext |= h.kind == MECH_CABUF && h.n > 0 ? 1 : 0;
-    a.tiles = (const int *)(c->buf + c->L.off_tiles);
-    a.n_tiles = (int)c->n_tiles;
     a.row = 1 + (int)c->slots.size();
+    a.tiles = (const int *)(c->buf + c->L.off_tiles) + l.first * a.row;
+    a.n_tiles = (int)l.n_tiles;
     a.kdev = (const long long *)(c->buf + c->L.off_kdev);
     a.kofs = kofs;
-    a.xcd_order = (c->launch_flags & MECH_LAUNCH_XCD_ORDER) ? 1 : 0;
-    a.nontemporal = (c->launch_flags & MECH_LAUNCH_NONTEMPORAL) ? 1 : 0;
+    a.xcd_order = (l.flags & MECH_LAUNCH_XCD_ORDER) ? 1 : 0;
+    a.nontemporal = (l.flags & MECH_LAUNCH_NONTEMPORAL) ? 1 : 0;
     a.err = (int *)(c->buf + c->L.off_err);
     a.g = g;
     a.nd = c->nd;
     return a;
 }
 
-int fused_grid(const mech_ctx *c) {
-    int gr = (int)c->n_tiles;
-    if (c->blocks_per_cu > 0) gr = (int)std::min<int64_t>(c->n_tiles, (int64_t)c->blocks_per_cu * c->n_cu);
+int fused_grid(const mech_ctx *c, const Launch &l) {
+    int gr = (int)l.n_tiles;
+    if (l.blocks_per_cu > 0) gr = (int)std::min<int64_t>(l.n_tiles, (int64_t)l.blocks_per_cu * c->n_cu);
     return gr;
 }
 
@@ -483,8 +513,9 @@ int fused_grid(const mech_ctx *c) {
 // follows it on the same stream to provide v_{k+1}.
 int launch_fused_phase(mech_ctx *c, int phases, int vmode, const GlobDev &g, int kofs, hipStream_t s) {
     const int vm = vmode == MECH_V_CABLE ? MECH_V_EXTERNAL : vmode;
-    const int tn = (int)std::max<int64_t>(c->max_tile_nodes, 1);
-    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, g, kofs), fused_grid(c), c->block, tn, s));
+    const Launch &l = c->batched();
+    const int tn = (int)std::max<int64_t>(l.max_nodes, 1);
+    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, l, g, kofs), fused_grid(c, l), l.block, tn, s));
     if (vmode == MECH_V_CABLE && (phases & kDoCur)) HIPCHK(c, launch_cable(c->cable, c->nd, g, s));
     return MECH_OK;
 }
@@ -587,8 +618,8 @@ size_t res_lds_need(mech_ctx *c, int vmode, bool ion) {
     if (hit != c->res_lds_cache.end()) return hit->second;
     const int ns = (int)c->slots.size(), row = 1 + ns, ss = c->fp32 ? 4 : 8;
     size_t need = 0;
-    for (int64_t t = 0; t < c->n_tiles; ++t) {
-        const int32_t *r0 = c->tile_rows.data() + (size_t)t * row, *r1 = r0 + row;
+    for (int64_t t = 0; t < c->set.n_tiles; ++t) {
+        const int32_t *r0 = c->set.rows.data() + (size_t)t * row, *r1 = r0 + row;
         size_t b = res_node_bytes(r1[0] - r0[0], vmode, c->has_syn, ion);
         for (int s = 0; s < ns; ++s) b += res_slot_bytes(c->slots[s].kind, r1[1 + s] - r0[1 + s], ss);
         need = std::max(need, b);
@@ -625,14 +656,14 @@ int step_resident(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode)
         c->res_lds_allowed = cap;
     }
     if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
-    const FusedArgs a = fused_args(c, g, 0);
+    const FusedArgs a = fused_args(c, c->set, g, 0);
     for (int64_t done = 0; done < nsteps;) {
         const int n = (int)std::min<int64_t>(c->res_steps, nsteps - done);
         r.k0 = k0 + done;
         r.nsub = n;
         r.first_state = done > 0 ? 1 : 0;
         r.last_state = done + n == nsteps ? 1 : 0;
-        HIPCHK(c, launch_resident(c->fp32, vmode, a, r, fused_grid(c), c->block, need, c->stream));
+        HIPCHK(c, launch_resident(c->fp32, vmode, a, r, fused_grid(c, c->set), c->set.block, need, c->stream));
         done += n;
     }
     return MECH_OK;
@@ -763,7 +794,8 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
     {
         // the fused paths sum a node's contributions in fixed point, exact up
         // to kMaxPerNode of them
-        std::vector<int32_t> per(n_nodes, 0);
+        std::vector<int32_t> &per = c->per_node;
+        per.assign(n_nodes, 0);
         for (const SlotHost &h : c->slots)
             for (int32_t n : h.ni)
                 if (++per[n] > kMaxPerNode) {
@@ -824,7 +856,17 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
             c->nd.cai = (double *)(c->buf + c->L.off_ion);
             c->nd.ica = c->nd.cai + std::max<int64_t>(n_nodes, 1);
         }
-        rc = build_tiles(c);
+        make_tiles(c, c->set);
+        rc = upload_tiles(c, c->set, 0);
+    }
+    if (rc == MECH_OK) {
+        // the table region holds the tables of both shapes (it is sized for
+        // tiles of 64 instances); only a context of a few nodes has no room
+        c->fit = fit_launch(c);
+        make_tiles(c, c->fit);
+        const size_t row = 1 + c->slots.size(), first = c->set.rows.size() / row;
+        if (first + c->fit.rows.size() / row <= (size_t)c->L.max_tile_rows) rc = upload_tiles(c, c->fit, first);
+        else c->fit = c->set;
     }
     if (rc != MECH_OK) {
         g_last_error = c->err;
@@ -1238,29 +1280,32 @@ int mech_set_launch(mech_ctx *c, int block, int tile_instances, int tile_nodes, 
     if (tile_nodes < kMinTileNodes || tile_nodes > kMaxTileNodes)
         return fail(c, MECH_ERR_INVAL, "tile_nodes must be in [%d, %d]", kMinTileNodes, kMaxTileNodes);
     if (blocks_per_cu < 0 || blocks_per_cu > 64) return fail(c, MECH_ERR_INVAL, "blocks_per_cu must be 0..64");
-    c->block = block;
-    c->tile_budget = tile_instances;
-    c->tile_nodes = tile_nodes;
-    c->blocks_per_cu = blocks_per_cu;
-    c->launch_flags = flags;
-    return build_tiles(c);
+    c->set.block = block;
+    c->set.budget = tile_instances;
+    c->set.nodes = tile_nodes;
+    c->set.blocks_per_cu = blocks_per_cu;
+    c->set.flags = flags;
+    c->chosen = true;
+    make_tiles(c, c->set);
+    return upload_tiles(c, c->set, 0);
 }
 
 int mech_get_launch(const mech_ctx *c, int *block, int *tile_instances, int *tile_nodes, int *blocks_per_cu,
                     int *flags) {
     if (!c) return fail(nullptr, MECH_ERR_INVAL, "null ctx");
-    if (flags) *flags = c->launch_flags;
-    if (block) *block = c->block;
-    if (tile_instances) *tile_instances = c->tile_budget;
-    if (tile_nodes) *tile_nodes = c->tile_nodes;
-    if (blocks_per_cu) *blocks_per_cu = c->blocks_per_cu;
+    const Launch &l = c->batched();
+    if (flags) *flags = l.flags;
+    if (block) *block = l.block;
+    if (tile_instances) *tile_instances = l.budget;
+    if (tile_nodes) *tile_nodes = l.nodes;
+    if (blocks_per_cu) *blocks_per_cu = l.blocks_per_cu;
     return MECH_OK;
 }
 
 int mech_info(const mech_ctx *c, int64_t *n_tiles, int64_t *max_tile_nodes) {
     if (!c) return fail(nullptr, MECH_ERR_INVAL, "null ctx");
-    if (n_tiles) *n_tiles = c->n_tiles;
-    if (max_tile_nodes) *max_tile_nodes = c->max_tile_nodes;
+    if (n_tiles) *n_tiles = c->batched().n_tiles;
+    if (max_tile_nodes) *max_tile_nodes = c->batched().max_nodes;
     return MECH_OK;
 }
 
@@ -1296,7 +1341,8 @@ static int autotune_impl(mech_ctx *c, double dt, int vmode, int nsteps, int reps
     };
     hipError_t e = copy_all(true);
     if (e != hipSuccess) { (void)hipFree(save); return fail(c, MECH_ERR_HIP, "autotune save: %s", hipGetErrorString(e)); }
-    int best[5] = {c->block, c->tile_budget, c->tile_nodes, c->blocks_per_cu, c->launch_flags};
+    const Launch &now = resident ? c->set : c->batched();
+    int best[5] = {now.block, now.budget, now.nodes, now.blocks_per_cu, now.flags};
     double best_t = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     (void)hipEventCreate(&e0);
