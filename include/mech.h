@@ -125,7 +125,10 @@ enum { MECH_V_EXTERNAL = 0, MECH_V_CLAMP = 1, MECH_V_ISOLATED = 2, MECH_V_CABLE 
  *        eagerly (the paper's per-mechanism kernel structure);
  * BATCHED: per step one fused launch over a table of node tiles that runs
  *        state(k-1), events(k) and cur(k) of every type and provides the
- *        next voltage, with chunks of steps replayed from a HIP graph.  Each
+ *        next voltage, with chunks of steps replayed from a HIP graph (a
+ *        context whose instance arrays fit the L2 caches and whose launch
+ *        shape the caller has not set takes up to 256 such steps per launch
+ *        in the CLAMP and ISOLATED modes: the same arithmetic).  Each
  *        node's rhs, d (and calcium current) is summed in fixed point with
  *        resolution 2^-67 (each contribution rounded to a multiple of 2^-67,
  *        exactly when its magnitude is >= 2^-15) and rounded to double

@@ -111,8 +111,9 @@ struct FusedArgs {
     const int *tiles;          // (n_tiles + 1) rows of (1 + n_slots) ints
     int n_tiles;
     int row;                   // 1 + n_slots
-    const long long *kdev;     // step counter in device memory
-    int kofs;                  // k = *kdev + kofs
+    const long long *kdev;     // step counter in device memory (graphs), or null
+    long long kbase;           // the step without it
+    int kofs;                  // k = (*kdev or kbase) + kofs
     int xcd_order;             // XCD-contiguous tile order (launch flag bit 0)
     int nontemporal;           // non-temporal SoA streams (launch flag bit 1)
     int *err;
@@ -212,6 +213,8 @@ hipError_t launch_cable_coeffs(const CableDev &c, const double *area, hipStream_
 hipError_t launch_fused(bool fp32, int phases, int vmode, const FusedArgs &a, int grid, int block, int tile_nodes,
                         hipStream_t s);
 size_t fused_lds_bytes(int tile_nodes, bool ion);
+hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int block, int tile_nodes, hipStream_t s);
+size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion);
 hipError_t fused_allow_lds(size_t bytes);
 hipError_t launch_resident(bool fp32, int vmode, const FusedArgs &a, const ResArgs &r, int grid, int block,
                            size_t lds_bytes, hipStream_t s);

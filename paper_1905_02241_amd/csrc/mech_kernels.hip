@@ -1512,6 +1512,35 @@ __device__ __forceinline__ int tile_of(int b, int T, int xcd_order) {
     return x * q + min(x, r) + j;
 }
 
+// Every instance of a tile.
+template <class S, int PH, bool NT, bool EXT>
+__device__ __forceinline__ void tile_pass(const FusedArgs &a, const int *r0, const int *r1, int nlo, const double *vl,
+                                          const double *sc, Acc ar, Acc ad, const double *cl, Acc ai, long long k,
+                                          bool ion, int &flag) {
+    int first = 0;
+    for (int s = 0; s < a.n_slots; ++s) {
+        const SlotDev &sl = a.slot[s];
+        const int lo = r0[1 + s], hi = r1[1 + s];
+        switch (sl.kind) {
+        case MECH_PAS:
+            if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
+            break;
+        case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+        case MECH_CABUF:
+            if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
+            break;
+        default: break;
+        }
+        if (!(sl.kind == MECH_PAS && !(PH & kDoCur))) first += (hi - lo + 63) & ~63;
+        while (first >= (int)blockDim.x) first -= (int)blockDim.x;
+    }
+}
+
 // EXT: the extended instantiations, which add the buffered-calcium type and
 // the shared calcium ion (a run-time switch there).  They are kept apart so
 // that the default instantiations keep their register budget.
@@ -1524,7 +1553,7 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
     double *cl = lds + 6 * tn;
     const Acc ai{w + 7 * tn, w + 8 * tn};
     const bool ion = EXT && a.g.shared_ca;
-    const long long k = *a.kdev + a.kofs;
+    const long long k = (a.kdev ? *a.kdev : a.kbase) + a.kofs;
     int flag = 0;
     for (int b = blockIdx.x; b < a.n_tiles; b += gridDim.x) {
         const int t = tile_of(b, a.n_tiles, a.xcd_order);
@@ -1544,28 +1573,7 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
             }
         }
         __syncthreads();
-        int first = 0;
-        for (int s = 0; s < a.n_slots; ++s) {
-            const SlotDev &sl = a.slot[s];
-            const int lo = r0[1 + s], hi = r1[1 + s];
-            switch (sl.kind) {
-            case MECH_PAS:
-                if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
-                break;
-            case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-            case MECH_CABUF:
-                if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
-                break;
-            default: break;
-            }
-            if (!(sl.kind == MECH_PAS && !(PH & kDoCur))) first += (hi - lo + 63) & ~63;
-            while (first >= (int)blockDim.x) first -= (int)blockDim.x;
-        }
+        tile_pass<S, PH, NT, EXT>(a, r0, r1, nlo, vl, sc, ar, ad, cl, ai, k, ion, flag);
         if (PH & kDoCur) {
             __syncthreads();
             for (int j = threadIdx.x; j < nn; j += blockDim.x) {
@@ -1585,6 +1593,105 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
                     a.nd.cai[n] = c;
                     a.nd.ica[n] = ica;
                 }
+            }
+        }
+        __syncthreads();
+    }
+    if (flag) atomicOr(a.err, 1);
+}
+
+// -------------------------------------------------- several steps a launch --
+// A tile's middle steps in one launch, for contexts whose instance arrays stay
+// in the L2s from one step to the next: launches and the reading of the tile's
+// nodes, not the arrays, are then most of a step.  Each step is k_fused's,
+// STATEs are loaded and stored in every one of them (always by the same
+// thread, so that no step waits for another's stores to be visible), the
+// tile's node data stays in LDS, and rhs, d, v, spikes and the node ion are
+// written after the last step.  Clamp and isolated modes, whose tiles do not
+// depend on each other.
+// us per step, a launch each (from graphs) / 256 a launch: 10 k hh 5.4 / 2.9,
+// 67 k hh+pas in FP32 6.3 / 2.4, 67 k of C5's mix in FP32 7.1 / 3.3, 15 k of
+// eight types 11.7 / 9.5, 266 k synapses 8.6 / 5.5.
+template <class S, int VM, bool EXT>
+__global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
+    extern __shared__ double lds[];
+    constexpr int PH = kDoCur | kDoState;
+    const bool ion = EXT && a.g.shared_ca;
+    const bool syn = a.has_syn != 0;
+    int flag = 0;
+    const int t = tile_of((int)blockIdx.x, a.n_tiles, a.xcd_order);
+    const int *r0 = a.tiles + (size_t)t * a.row;
+    const int *r1 = r0 + a.row;
+    const int nlo = r0[0], nn = r1[0] - nlo;
+    unsigned long long *w = (unsigned long long *)lds;
+    double *vl = lds, *q = lds + 5 * nn;
+    const Acc ar{w + nn, w + 2 * nn}, ad{w + 3 * nn, w + 4 * nn};
+    double *sc = q;
+    if (syn) q += nn;
+    double *md = q;   // 1e-3 cm/dt (isolated) or the clamp waveform, 4 per node
+    q += (VM == MECH_V_CLAMP ? 4 : 1) * nn;
+    double *cl = q;
+    const Acc ai{(unsigned long long *)q + nn, (unsigned long long *)q + 2 * nn};
+    if (ion) q += 3 * nn;
+    int *spk = (int *)q;
+    for (int j = threadIdx.x; j < nn; j += blockDim.x) {
+        const int n = nlo + j;
+        vl[j] = a.nd.v[n];
+        fx_zero(ar, j);
+        fx_zero(ad, j);
+        if (syn) sc[j] = 1e2 / a.nd.area[n];
+        if (VM == MECH_V_CLAMP) {
+            md[4 * j] = a.nd.c_off[n];
+            md[4 * j + 1] = a.nd.c_amp[n];
+            md[4 * j + 2] = a.nd.c_freq[n];
+            md[4 * j + 3] = a.nd.c_phase[n];
+        } else {
+            md[j] = 1e-3 * a.nd.cm[n] / a.g.dt;
+            spk[j] = 0;
+        }
+        if (ion) {
+            cl[j] = a.nd.cai[n];
+            fx_zero(ai, j);
+        }
+    }
+    __syncthreads();
+    for (int sub = 0; sub < nsteps; ++sub) {
+        const long long k = a.kbase + sub;
+        tile_pass<S, PH, false, EXT>(a, r0, r1, nlo, vl, sc, ar, ad, cl, ai, k, ion, flag);
+        __syncthreads();
+        const bool last = sub + 1 == nsteps;
+        for (int j = threadIdx.x; j < nn; j += blockDim.x) {
+            const int n = nlo + j;
+            const double rr = fx_get(ar, j), dd = fx_get(ad, j), v0 = vl[j];
+            double v1;
+            if (VM == MECH_V_ISOLATED) {
+                v1 = v0 + rr / (md[j] + dd);
+                if (v0 < a.g.vthresh && v1 >= a.g.vthresh) spk[j] += 1;
+            } else {
+                const double t1 = (double)(k + 1) * a.g.dt;
+                v1 = md[4 * j] + md[4 * j + 1] * sin_d(2.0 * 3.14159265358979323846 * md[4 * j + 2] * t1 * 1e-3 +
+                                                     md[4 * j + 3]);
+            }
+            vl[j] = v1;
+            fx_zero(ar, j);
+            fx_zero(ad, j);
+            if (ion) {
+                double c = cl[j];
+                const double ica = fx_get(ai, j);
+                ion_pool(a.g, ica, c);
+                flag |= bad(c);
+                cl[j] = c;
+                fx_zero(ai, j);
+                if (last) {
+                    a.nd.cai[n] = c;
+                    a.nd.ica[n] = ica;
+                }
+            }
+            if (last) {
+                a.nd.rhs[n] = rr;
+                a.nd.d[n] = dd;
+                a.nd.v[n] = v1;
+                if (VM == MECH_V_ISOLATED && spk[j]) a.nd.spikes[n] += spk[j];
             }
         }
         __syncthreads();
@@ -2229,6 +2336,23 @@ static hipError_t fused_t(int phases, int vmode, const FusedArgs &a, int grid, i
     default: return fused_vm<S, kDoCur | kDoState, NT, EXT>(vmode, a, grid, block, lds, tn, s);
     }
 }
+size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion) {
+    return (size_t)tile_nodes * (8 * res_node_doubles(vmode, syn, ion) + 4);
+}
+template <class S, bool EXT>
+static hipError_t steps_t(int vmode, const FusedArgs &a, int nsteps, int block, size_t lds, hipStream_t s) {
+    if (vmode == MECH_V_CLAMP) k_steps<S, MECH_V_CLAMP, EXT><<<a.n_tiles, block, lds, s>>>(a, nsteps);
+    else k_steps<S, MECH_V_ISOLATED, EXT><<<a.n_tiles, block, lds, s>>>(a, nsteps);
+    return hipGetLastError();
+}
+hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int block, int tn, hipStream_t s) {
+    if (a.n_tiles == 0 || nsteps <= 0) return hipSuccess;
+    const bool ext = a.g.shared_ca || a.has_ext;
+    const size_t lds = steps_lds_bytes(tn, vmode, a.has_syn != 0, a.g.shared_ca != 0);
+    if (ext) return fp32 ? steps_t<float, true>(vmode, a, nsteps, block, lds, s) : steps_t<double, true>(vmode, a, nsteps, block, lds, s);
+    return fp32 ? steps_t<float, false>(vmode, a, nsteps, block, lds, s) : steps_t<double, false>(vmode, a, nsteps, block, lds, s);
+}
+
 size_t fused_lds_bytes(int tile_nodes, bool ion) { return (ion ? 9 : 6) * 8 * (size_t)tile_nodes; }
 
 // Lets every fused instantiation take up to `bytes` of dynamic LDS.
@@ -2245,8 +2369,12 @@ hipError_t fused_allow_lds(size_t bytes) {
         (const void *)k_fused<S, kDoCur | kDoState, MECH_V_ISOLATED, NT, EXT>
         MECH_FUSED_FNS(double, false, false), MECH_FUSED_FNS(float, false, false),
         MECH_FUSED_FNS(double, true, false), MECH_FUSED_FNS(float, true, false),
-        MECH_FUSED_FNS(double, false, true), MECH_FUSED_FNS(float, false, true)
+        MECH_FUSED_FNS(double, false, true), MECH_FUSED_FNS(float, false, true),
 #undef MECH_FUSED_FNS
+        (const void *)k_steps<double, MECH_V_CLAMP, false>, (const void *)k_steps<double, MECH_V_CLAMP, true>,
+        (const void *)k_steps<double, MECH_V_ISOLATED, false>, (const void *)k_steps<double, MECH_V_ISOLATED, true>,
+        (const void *)k_steps<float, MECH_V_CLAMP, false>, (const void *)k_steps<float, MECH_V_CLAMP, true>,
+        (const void *)k_steps<float, MECH_V_ISOLATED, false>, (const void *)k_steps<float, MECH_V_ISOLATED, true>
     };
     for (const void *f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b);

@@ -484,7 +484,8 @@ int launch_plain_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int a
     return MECH_OK;
 }
 
-FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int kofs) {
+// `k`: the step, or -1 to take it from the device counter plus kofs (graphs).
+FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, int kofs) {
     FusedArgs a{};
     for (int s = 0; s < (int)c->slots.size(); ++s) a.slot[s] = slot_dev(c, s);
     a.n_slots = (int)c->slots.size();
@@ -493,7 +494,8 @@ FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int kofs) {
     a.row = 1 + (int)c->slots.size();
     a.tiles = (const int *)(c->buf + c->L.off_tiles) + l.first * a.row;
     a.n_tiles = (int)l.n_tiles;
-    a.kdev = (const long long *)(c->buf + c->L.off_kdev);
+    a.kdev = k < 0 ? (const long long *)(c->buf + c->L.off_kdev) : nullptr;
+    a.kbase = k < 0 ? 0 : k;
     a.kofs = kofs;
     a.xcd_order = (l.flags & MECH_LAUNCH_XCD_ORDER) ? 1 : 0;
     a.nontemporal = (l.flags & MECH_LAUNCH_NONTEMPORAL) ? 1 : 0;
@@ -511,11 +513,11 @@ int fused_grid(const mech_ctx *c, const Launch &l) {
 
 // One fused pass; in cable mode the pass only writes rhs/d and the tree solve
 // follows it on the same stream to provide v_{k+1}.
-int launch_fused_phase(mech_ctx *c, int phases, int vmode, const GlobDev &g, int kofs, hipStream_t s) {
+int launch_fused_phase(mech_ctx *c, int phases, int vmode, const GlobDev &g, int64_t k, int kofs, hipStream_t s) {
     const int vm = vmode == MECH_V_CABLE ? MECH_V_EXTERNAL : vmode;
     const Launch &l = c->batched();
     const int tn = (int)std::max<int64_t>(l.max_nodes, 1);
-    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, l, g, kofs), fused_grid(c, l), l.block, tn, s));
+    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, l, g, k, kofs), fused_grid(c, l), l.block, tn, s));
     if (vmode == MECH_V_CABLE && (phases & kDoCur)) HIPCHK(c, launch_cable(c->cable, c->nd, g, s));
     return MECH_OK;
 }
@@ -534,7 +536,7 @@ int get_graph(mech_ctx *c, int vmode, double dt, const GlobDev &g, int n, hipGra
     HIPCHK(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
     int rc = MECH_OK;
     for (int j = 0; j < n && rc == MECH_OK; ++j)
-        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, j, c->capture_stream);
+        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, -1, j, c->capture_stream);
     hipError_t e1 = rc == MECH_OK ? launch_bump_k((long long *)(c->buf + c->L.off_kdev), n, c->capture_stream)
                                   : hipSuccess;
     hipGraph_t graph = nullptr;
@@ -568,17 +570,38 @@ int step_plain(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode) {
     return MECH_OK;
 }
 
+// Whether the batched path takes several steps per launch (k_steps): in the
+// modes whose tiles are independent, for a context in its own shape whose
+// instance arrays fit the L2s (8 x 4 MiB, a quarter left for node data).  A
+// launch per step would find them there too, so it costs its start-up alone:
+// 19 MB of synapses take 8.6 us a step with a launch each and 5.5 without.
+// Larger contexts stream their arrays from HBM whatever the launches.
+constexpr size_t kStepsBytes = (size_t)24 << 20;
+constexpr int kStepsMax = 256;
+bool several_steps(const mech_ctx *c, int vmode) {
+    return !c->chosen && (vmode == MECH_V_CLAMP || vmode == MECH_V_ISOLATED) && c->L.inst_end <= kStepsBytes;
+}
+
 int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, bool use_graph) {
     const GlobDev g = make_glob(c, dt);
-    long long *kdev = (long long *)(c->buf + c->L.off_kdev);
     if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
-    HIPCHK(c, launch_set_k(kdev, k0, c->stream));
-    int rc = launch_fused_phase(c, kDoCur, vmode, g, 0, c->stream);
+    int rc = launch_fused_phase(c, kDoCur, vmode, g, k0, 0, c->stream);
     if (rc) return rc;
-    // middle passes: state(k-1) + events(k) + cur(k) for k = k0+1 .. k0+nsteps-1,
-    // replayed from graphs of kGraphSteps passes and one of the remainder
-    int64_t mids = nsteps - 1;
-    HIPCHK(c, launch_set_k(kdev, k0 + 1, c->stream));
+    // middle passes: state(k-1) + events(k) + cur(k) for k = k0+1 .. k0+nsteps-1:
+    // several per launch, or replayed from graphs of kGraphSteps passes and one
+    // of the remainder
+    int64_t mids = nsteps - 1, k = k0 + 1;
+    if (several_steps(c, vmode)) {
+        const Launch &l = c->batched();
+        const int tn = (int)std::max<int64_t>(l.max_nodes, 1);
+        for (; mids > 0;) {
+            const int n = (int)std::min<int64_t>(mids, kStepsMax);
+            HIPCHK(c, launch_steps(c->fp32, vmode, fused_args(c, l, g, k, 0), n, l.block, tn, c->stream));
+            mids -= n;
+            k += n;
+        }
+    }
+    if (use_graph && mids > 0) HIPCHK(c, launch_set_k((long long *)(c->buf + c->L.off_kdev), k, c->stream));
     while (use_graph && mids > 0) {
         const int n = (int)std::min<int64_t>(mids, kGraphSteps);
         hipGraphExec_t exec;
@@ -587,12 +610,12 @@ int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, 
         HIPCHK(c, hipGraphLaunch(exec, c->stream));
         mids -= n;
     }
-    for (int64_t j = 0; j < mids; ++j) {
-        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, (int)j, c->stream);
+    for (; mids > 0; --mids, ++k) {
+        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, k, 0, c->stream);
         if (rc) return rc;
     }
     // closing state update at v_{k0+nsteps}
-    return launch_fused_phase(c, kDoState, MECH_V_EXTERNAL, g, 0, c->stream);
+    return launch_fused_phase(c, kDoState, MECH_V_EXTERNAL, g, k0 + nsteps, 0, c->stream);
 }
 
 // ------------------------------------------------------ time-fused path --
@@ -656,7 +679,7 @@ int step_resident(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode)
         c->res_lds_allowed = cap;
     }
     if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
-    const FusedArgs a = fused_args(c, c->set, g, 0);
+    const FusedArgs a = fused_args(c, c->set, g, 0, 0);
     for (int64_t done = 0; done < nsteps;) {
         const int n = (int)std::min<int64_t>(c->res_steps, nsteps - done);
         r.k0 = k0 + done;

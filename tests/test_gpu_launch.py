@@ -31,3 +31,18 @@ def test_own_shape_gives_the_same_bits(make, n):
     a, _ = run_gpu(w, steps, "batched", "fp64")
     b, _ = run_gpu(w, steps, "batched", "fp64", launch=(128, 256, 128, 0, 0))
     same(a, b)
+
+
+@pytest.mark.parametrize("vmode", ["clamp", "isolated"])
+@pytest.mark.parametrize("shared_ca", [0, 1])
+@pytest.mark.parametrize("steps", [2, 3, 260])
+def test_several_steps_a_launch_give_the_same_bits(vmode, shared_ca, steps):
+    """Every type, ragged tiles, from no middle step to more than one launch
+    holds, against a launch per step (a shape set by the caller)."""
+    w = W.make_tiny(82, kinds=W.KINDS, n_nodes=777, vmode=vmode, syn_per_node=5.0, event_rate_hz=300.0)
+    w.globals["shared_ca"] = shared_ca
+    a, ma = run_gpu(w, steps, "batched", "fp64")
+    b, mb = run_gpu(w, steps, "batched", "fp64", launch=(128, 256, 128, 0, 0))
+    same(a, b)
+    for name in ("cai", "ica"):
+        assert np.array_equal(ma.ion(name), mb.ion(name)), name
