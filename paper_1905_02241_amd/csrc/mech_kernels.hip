@@ -1600,6 +1600,144 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
     if (flag) atomicOr(a.err, 1);
 }
 
+// ------------------------------------------- single phases in one launch --
+// mech_cur and mech_state for callers that solve for v themselves: every type
+// in one launch, where the per-type launches (two for a type with several
+// instances on a node, and a fill) cost a small context far more than their
+// work.  A step of cur, the caller's solve in two torch calls and state, with
+// launches per type / with one each: 15 k instances of eight types 94 / 21 us,
+// 100 k of C5's mix 46 / 17, 1 M 62 / 33, 8.3 M 267 / 245.
+//
+// The current update works on the fused path's node tiles and keeps FP64 sums
+// in a fixed order without atomics: instances leave their contributions in
+// LDS, then a thread per node adds its node's, type by type in instance order.
+// LDS: per node v and 100/area, then the first contribution of each type
+// (kNoFirst: none), per instance the contributions and the tile-local node.
+constexpr unsigned short kNoFirst = 0xffff;
+
+template <class S, int KIND>
+__device__ __forceinline__ void phase_cur_slot(const FusedArgs &a, const SlotDev &sl, int lo, int hi, int first, int at, int nlo,
+                                               const double *vl, const double *sc, double *cx, double *cy, double *cz,
+                                               unsigned short *nj, unsigned short *start, bool ion, int &flag) {
+    int t = (int)threadIdx.x - first;
+    if (t < 0) t += (int)blockDim.x;
+    for (int i = lo + t; i < hi; i += (int)blockDim.x) {
+        const int n = sl.ni[i], j = n - nlo, q = at + i - lo;
+        const bool head = i == lo || sl.ni[i - 1] != n;
+        double ci, cg, ica = 0.0;
+        if (is_ca_kind(KIND) && ion) ca_shared<S, kDoCur>(sl, i, vl[j], a.nd.cai[n], a.g, ci, cg, ica, flag);
+        else instance<S, KIND, kDoCur>(sl, i, vl[j], a.g, a.kbase, ci, cg, flag);
+        if (KIND == MECH_SYN) {
+            ci *= sc[j];
+            cg *= sc[j];
+        }
+        cx[q] = ci;
+        cy[q] = cg;
+        if (ion) cz[q] = ica;
+        nj[q] = (unsigned short)j;
+        if (head) start[j] = (unsigned short)q;
+    }
+}
+
+template <class S>
+__global__ __launch_bounds__(256) void k_phase_cur(FusedArgs a, int accumulate, int tn, int ti) {
+    extern __shared__ double lds[];
+    const bool ion = a.g.shared_ca != 0;
+    double *vl = lds, *sc = vl + tn, *cx = sc + tn, *cy = cx + ti, *cz = cy + ti;
+    unsigned short *nj = (unsigned short *)(ion ? cz + ti : cz), *start = nj + ti;
+    const int t = tile_of((int)blockIdx.x, a.n_tiles, a.xcd_order);
+    const int *r0 = a.tiles + (size_t)t * a.row;
+    const int *r1 = r0 + a.row;
+    const int nlo = r0[0], nn = r1[0] - nlo;
+    int flag = 0;
+    for (int j = threadIdx.x; j < nn; j += blockDim.x) {
+        vl[j] = a.nd.v[nlo + j];
+        if (a.has_syn) sc[j] = 1e2 / a.nd.area[nlo + j];
+        for (int s = 0; s < a.n_slots; ++s) start[s * tn + j] = kNoFirst;
+    }
+    __syncthreads();
+    int first = 0, at = 0;
+    for (int s = 0; s < a.n_slots; ++s) {
+        const SlotDev &sl = a.slot[s];
+        const int lo = r0[1 + s], hi = r1[1 + s];
+        unsigned short *st = start + s * tn;
+        switch (sl.kind) {
+#define MECH_PHASE_CASE(K)                                                                                          \
+    case K: phase_cur_slot<S, K>(a, sl, lo, hi, first, at, nlo, vl, sc, cx, cy, cz, nj, st, ion, flag); break;
+        MECH_PHASE_CASE(MECH_PAS)
+        MECH_PHASE_CASE(MECH_HH)
+        MECH_PHASE_CASE(MECH_IH)
+        MECH_PHASE_CASE(MECH_CAHVA)
+        MECH_PHASE_CASE(MECH_SYN)
+        MECH_PHASE_CASE(MECH_KMARKOV)
+        MECH_PHASE_CASE(MECH_CAPUMP)
+        MECH_PHASE_CASE(MECH_CABUF)
+#undef MECH_PHASE_CASE
+        default: break;
+        }
+        at += hi - lo;
+        first += (hi - lo + 63) & ~63;
+        while (first >= (int)blockDim.x) first -= (int)blockDim.x;
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < nn; j += blockDim.x) {
+        double r = 0.0, d = 0.0, z = 0.0;
+        int end = 0;
+        for (int s = 0; s < a.n_slots; ++s) {
+            end += r1[1 + s] - r0[1 + s];
+            const int q0 = start[s * tn + j];
+            if (q0 == kNoFirst) continue;
+            for (int q = q0; q < end && nj[q] == j; ++q) {
+                r -= cx[q];
+                d += cy[q];
+                if (ion) z += cz[q];
+            }
+        }
+        const int n = nlo + j;
+        a.nd.rhs[n] = accumulate ? a.nd.rhs[n] + r : r;
+        a.nd.d[n] = accumulate ? a.nd.d[n] + d : d;
+        if (ion) a.nd.ica[n] = accumulate ? a.nd.ica[n] + z : z;
+    }
+    if (flag) atomicOr(a.err, 1);
+}
+
+// The state update of every type: blocks of 256 instances, a type's blocks one
+// after the other.
+template <class S>
+__global__ __launch_bounds__(256) void k_phase_state(FusedArgs a) {
+    int b = (int)blockIdx.x, s = 0;
+    for (; s < a.n_slots; ++s) {
+        const int nb = a.slot[s].kind == MECH_PAS ? 0 : (a.slot[s].n + 255) >> 8;
+        if (b < nb) break;
+        b -= nb;
+    }
+    if (s == a.n_slots) return;
+    const SlotDev &sl = a.slot[s];
+    const int i = b * 256 + (int)threadIdx.x;
+    if (i >= sl.n) return;
+    const double v = a.nd.v[sl.ni[i]];
+    double ci, cg, ica;
+    int flag = 0;
+    if (is_ca_kind(sl.kind) && a.g.shared_ca) {
+        ca_shared<S, kDoState>(sl, i, v, 0.0, a.g, ci, cg, ica, flag);
+    } else {
+        switch (sl.kind) {
+#define MECH_PHASE_CASE(K)                                              \
+    case K: instance<S, K, kDoState>(sl, i, v, a.g, 0, ci, cg, flag); break;
+        MECH_PHASE_CASE(MECH_HH)
+        MECH_PHASE_CASE(MECH_IH)
+        MECH_PHASE_CASE(MECH_CAHVA)
+        MECH_PHASE_CASE(MECH_SYN)
+        MECH_PHASE_CASE(MECH_KMARKOV)
+        MECH_PHASE_CASE(MECH_CAPUMP)
+        MECH_PHASE_CASE(MECH_CABUF)
+#undef MECH_PHASE_CASE
+        default: break;
+        }
+    }
+    if (flag) atomicOr(a.err, 1);
+}
+
 // -------------------------------------------------- several steps a launch --
 // A tile's middle steps in one launch, for contexts whose instance arrays stay
 // in the L2s from one step to the next: launches and the reading of the tile's
@@ -2336,6 +2474,26 @@ static hipError_t fused_t(int phases, int vmode, const FusedArgs &a, int grid, i
     default: return fused_vm<S, kDoCur | kDoState, NT, EXT>(vmode, a, grid, block, lds, tn, s);
     }
 }
+size_t phase_lds_bytes(int tile_nodes, int tile_instances, int n_slots, bool ion) {
+    return 16 * (size_t)tile_nodes + (ion ? 26 : 18) * (size_t)tile_instances + 2 * (size_t)n_slots * tile_nodes;
+}
+hipError_t launch_phase_cur(bool fp32, const FusedArgs &a, int accumulate, int tn, int ti, hipStream_t s) {
+    if (a.n_tiles == 0) return hipSuccess;
+    const size_t lds = phase_lds_bytes(tn, ti, a.n_slots, a.g.shared_ca != 0);
+    if (fp32) k_phase_cur<float><<<a.n_tiles, 256, lds, s>>>(a, accumulate, tn, ti);
+    else k_phase_cur<double><<<a.n_tiles, 256, lds, s>>>(a, accumulate, tn, ti);
+    return hipGetLastError();
+}
+hipError_t launch_phase_state(bool fp32, const FusedArgs &a, hipStream_t s) {
+    long long nb = 0;
+    for (int i = 0; i < a.n_slots; ++i)
+        if (a.slot[i].kind != MECH_PAS) nb += (a.slot[i].n + 255) / 256;
+    if (nb == 0) return hipSuccess;
+    if (fp32) k_phase_state<float><<<(unsigned)nb, 256, 0, s>>>(a);
+    else k_phase_state<double><<<(unsigned)nb, 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
 size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion) {
     return (size_t)tile_nodes * (8 * res_node_doubles(vmode, syn, ion) + 4);
 }

@@ -186,7 +186,7 @@ void compute_layout(int64_t n_nodes, std::vector<SlotHost> &slots, int prec, Lay
 // A launch shape of the fused paths and its tile table.
 struct Launch {
     int block = 256, budget = 2048, nodes = 1024, blocks_per_cu = 0, flags = MECH_LAUNCH_XCD_ORDER;
-    int64_t n_tiles = 0, max_nodes = 0;
+    int64_t n_tiles = 0, max_nodes = 0, max_instances = 0;
     size_t first = 0;                 // first row in the device's table region
     std::vector<int32_t> rows;        // host copy of the tile table
 };
@@ -352,12 +352,13 @@ void make_tiles(const mech_ctx *c, Launch &l) {
                                       : (int32_t)(std::lower_bound(h.ni.begin(), h.ni.end(), (int32_t)node) - h.ni.begin()));
     };
     push(0);
-    int64_t cost = 0, nodes = 0, max_nodes = 0;
+    int64_t cost = 0, nodes = 0, max_nodes = 0, max_cost = 0;
     for (int64_t n = 0; n < c->n_nodes; ++n) {
         const int64_t cn = c->per_node[n];
         if (nodes > 0 && (cost + cn > l.budget || nodes >= l.nodes)) {
             push(n);
             max_nodes = std::max(max_nodes, nodes);
+            max_cost = std::max(max_cost, cost);
             cost = 0;
             nodes = 0;
         }
@@ -365,9 +366,11 @@ void make_tiles(const mech_ctx *c, Launch &l) {
         ++nodes;
     }
     max_nodes = std::max(max_nodes, nodes);
+    max_cost = std::max(max_cost, cost);
     push(c->n_nodes);
     l.n_tiles = c->n_nodes > 0 ? (int64_t)rows.size() / (1 + (int64_t)c->slots.size()) - 1 : 0;
     l.max_nodes = max_nodes;
+    l.max_instances = max_cost;
 }
 
 // Uploads the shape's tile table behind the first `first` rows.
@@ -503,6 +506,29 @@ FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, 
     a.g = g;
     a.nd = c->nd;
     return a;
+}
+
+// One phase as a call of its own (mech_cur, mech_state): every type in one
+// launch.  The current update needs a tile's contributions in LDS; a context
+// with thousands of instances on one node has a tile that is too large for
+// that and takes a launch per type (as does MECH_LAUNCH_PLAIN_ATOMIC, which
+// asks for that path's scatter).
+constexpr size_t kPhaseLds = 65536;
+int launch_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int accumulate) {
+    const Launch &l = c->fit;
+    const FusedArgs a = fused_args(c, l, g, k, 0);
+    if (!cur) {
+        HIPCHK(c, launch_phase_state(c->fp32, a, c->stream));
+        // the per-node calcium pools follow the gates, from this step's currents
+        if (g.shared_ca) HIPCHK(c, launch_ion_pool(c->nd, g, a.err, c->stream));
+        return MECH_OK;
+    }
+    const int tn = (int)std::max<int64_t>(l.max_nodes, 1), ti = (int)((l.max_instances + 3) & ~(int64_t)3);
+    if ((c->set.flags & MECH_LAUNCH_PLAIN_ATOMIC) || ti >= 0xffff ||
+        phase_lds_bytes(tn, ti, a.n_slots, g.shared_ca != 0) > kPhaseLds)
+        return launch_plain_phase(c, true, k, g, accumulate);
+    HIPCHK(c, launch_phase_cur(c->fp32, a, accumulate, tn, ti, c->stream));
+    return MECH_OK;
 }
 
 int fused_grid(const mech_ctx *c, const Launch &l) {
@@ -1257,7 +1283,7 @@ int mech_cur(mech_ctx *c, int64_t k, double dt, int accumulate) {
     if (rc) return rc;
     if (!(dt > 0.0) || k < 0) return fail(c, MECH_ERR_INVAL, "need dt > 0 and k >= 0");
     TraceRange range("mech_cur");
-    return launch_plain_phase(c, true, k, make_glob(c, dt), accumulate);
+    return launch_phase(c, true, k, make_glob(c, dt), accumulate);
 }
 
 int mech_state(mech_ctx *c, double dt) {
@@ -1266,7 +1292,7 @@ int mech_state(mech_ctx *c, double dt) {
     if (rc) return rc;
     if (!(dt > 0.0)) return fail(c, MECH_ERR_INVAL, "need dt > 0");
     TraceRange range("mech_state");
-    return launch_plain_phase(c, false, 0, make_glob(c, dt), 0);
+    return launch_phase(c, false, 0, make_glob(c, dt), 0);
 }
 
 int mech_step(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, int path) {

@@ -46,3 +46,65 @@ def test_several_steps_a_launch_give_the_same_bits(vmode, shared_ca, steps):
     same(a, b)
     for name in ("cai", "ica"):
         assert np.array_equal(ma.ion(name), mb.ion(name)), name
+
+
+def crowded():
+    """One node with more instances than a tile's LDS holds, its neighbours
+    with none or a few."""
+    w = W.make_tiny(83, kinds=("pas", "hh", "syn"), n_nodes=300, vmode="external", syn_per_node=2.0)
+    s = w.slots[0]
+    node = np.concatenate([s.node, np.full(5000, 7, dtype=np.int32)]).astype(np.int32)
+    s.params["g"] = np.concatenate([s.params["g"], np.full(5000, 1e-5)])
+    s.params["e"] = np.concatenate([s.params["e"], np.full(5000, -70.0)])
+    w.slots[0] = W.Slot("pas", node, s.params)
+    return w
+
+
+PHASES = {
+    "all": lambda: W.make_tiny(84, kinds=W.KINDS, n_nodes=333, per_node=2, syn_per_node=7.0, vmode="external",
+                               density_fraction=0.7),
+    # runs of one node longer than a wave
+    "runs": lambda: W.make_tiny(85, kinds=("pas", "syn"), n_nodes=11, per_node=1, syn_per_node=150.0, vmode="external"),
+    "one": lambda: W.make_tiny(86, kinds=("hh",), n_nodes=1, vmode="external"),
+    "crowded": crowded,
+}
+
+
+@pytest.mark.parametrize("shared_ca", [0, 1])
+@pytest.mark.parametrize("name", sorted(PHASES))
+def test_single_phases_match_the_oracle(name, shared_ca):
+    from oracle import oracle as O
+    from paper_1905_02241_amd import mech
+    from tests.parity import compare_nodes, compare_states
+    w = PHASES[name]()
+    if shared_ca and not any(s.kind in mech.CA_KINDS for s in w.slots):
+        pytest.skip("no calcium type")
+    w.globals["shared_ca"] = shared_ca
+    m = mech.from_workload(w, "fp64")
+    M = O.Model(w)
+    M.init()
+    rng = np.random.default_rng(9)
+    for k in range(6):
+        snap = {"states": mech.states_of(m), "v": m.nodes()["v"], "k": k}
+        if shared_ca:
+            snap["cai"] = m.ion("cai")
+        m.cur(k, w.dt)
+        M.events(k)
+        M.cur()
+        got = {**m.nodes(), "states": mech.states_of(m)}
+        compare_nodes({**got, "snap": snap}, M, "fp64", label=f"{name} cur k={k}", check_v=False)
+        v = rng.uniform(-80, 30, w.n_nodes)
+        m.set_node_array("v", v)
+        M.v[:] = v
+        m.state(w.dt)
+        M.state()
+        compare_states({"states": mech.states_of(m)}, M, "fp64", label=f"{name} state k={k}")
+    # accumulate: twice the currents of types without events
+    a = m.nodes()
+    if not any(s.kind == "syn" for s in w.slots):
+        m.cur(7, w.dt)
+        a = m.nodes()
+        m.cur(7, w.dt, accumulate=True)
+        b = m.nodes()
+        for key in ("rhs", "d"):
+            assert np.array_equal(b[key], 2.0 * a[key]), key
