@@ -111,9 +111,9 @@ struct FusedArgs {
     const int *tiles;          // (n_tiles + 1) rows of (1 + n_slots) ints
     int n_tiles;
     int row;                   // 1 + n_slots
-    const long long *kdev;     // step counter in device memory (graphs), or null
-    long long kbase;           // the step without it
-    int kofs;                  // k = (*kdev or kbase) + kofs
+    const long long *kdev;     // step counter in device memory: k = *kdev + kofs in a fused middle pass
+    long long kbase;           // k of a first pass, and of the first of several steps
+    int kofs;
     int xcd_order;             // XCD-contiguous tile order (launch flag bit 0)
     int nontemporal;           // non-temporal SoA streams (launch flag bit 1)
     int *err;

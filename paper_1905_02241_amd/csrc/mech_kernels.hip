@@ -1512,34 +1512,33 @@ __device__ __forceinline__ int tile_of(int b, int T, int xcd_order) {
     return x * q + min(x, r) + j;
 }
 
-// Every instance of a tile.
-template <class S, int PH, bool NT, bool EXT>
-__device__ __forceinline__ void tile_pass(const FusedArgs &a, const int *r0, const int *r1, int nlo, const double *vl,
-                                          const double *sc, Acc ar, Acc ad, const double *cl, Acc ai, long long k,
-                                          bool ion, int &flag) {
-    int first = 0;
-    for (int s = 0; s < a.n_slots; ++s) {
-        const SlotDev &sl = a.slot[s];
-        const int lo = r0[1 + s], hi = r1[1 + s];
-        switch (sl.kind) {
-        case MECH_PAS:
-            if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
-            break;
-        case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
-        case MECH_CABUF:
-            if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag);
-            break;
-        default: break;
-        }
-        if (!(sl.kind == MECH_PAS && !(PH & kDoCur))) first += (hi - lo + 63) & ~63;
-        while (first >= (int)blockDim.x) first -= (int)blockDim.x;
-    }
-}
+// Every instance of a tile.  A macro: as a function taking the arguments by
+// reference it cost the FP32 kernel 3 VGPRs and the FP64 one 8 % of its speed.
+#define MECH_TILE_PASS() \
+    do { \
+        int first = 0; \
+        for (int s = 0; s < a.n_slots; ++s) { \
+            const SlotDev &sl = a.slot[s]; \
+            const int lo = r0[1 + s], hi = r1[1 + s]; \
+            switch (sl.kind) { \
+            case MECH_PAS: \
+                if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); \
+                break; \
+            case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_CABUF: \
+                if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); \
+                break; \
+            default: break; \
+            } \
+            if (!(sl.kind == MECH_PAS && !(PH & kDoCur))) first += (hi - lo + 63) & ~63; \
+            while (first >= (int)blockDim.x) first -= (int)blockDim.x; \
+        } \
+    } while (0)
 
 // EXT: the extended instantiations, which add the buffered-calcium type and
 // the shared calcium ion (a run-time switch there).  They are kept apart so
@@ -1553,7 +1552,8 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
     double *cl = lds + 6 * tn;
     const Acc ai{w + 7 * tn, w + 8 * tn};
     const bool ion = EXT && a.g.shared_ca;
-    const long long k = (a.kdev ? *a.kdev : a.kbase) + a.kofs;
+    // middle passes (graphs) count from the device's step counter
+    const long long k = PH == (kDoCur | kDoState) ? *a.kdev + a.kofs : a.kbase;
     int flag = 0;
     for (int b = blockIdx.x; b < a.n_tiles; b += gridDim.x) {
         const int t = tile_of(b, a.n_tiles, a.xcd_order);
@@ -1573,7 +1573,7 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
             }
         }
         __syncthreads();
-        tile_pass<S, PH, NT, EXT>(a, r0, r1, nlo, vl, sc, ar, ad, cl, ai, k, ion, flag);
+        MECH_TILE_PASS();
         if (PH & kDoCur) {
             __syncthreads();
             for (int j = threadIdx.x; j < nn; j += blockDim.x) {
@@ -1754,6 +1754,7 @@ template <class S, int VM, bool EXT>
 __global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
     extern __shared__ double lds[];
     constexpr int PH = kDoCur | kDoState;
+    constexpr bool NT = false;
     const bool ion = EXT && a.g.shared_ca;
     const bool syn = a.has_syn != 0;
     int flag = 0;
@@ -1795,7 +1796,7 @@ __global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
     __syncthreads();
     for (int sub = 0; sub < nsteps; ++sub) {
         const long long k = a.kbase + sub;
-        tile_pass<S, PH, false, EXT>(a, r0, r1, nlo, vl, sc, ar, ad, cl, ai, k, ion, flag);
+        MECH_TILE_PASS();
         __syncthreads();
         const bool last = sub + 1 == nsteps;
         for (int j = threadIdx.x; j < nn; j += blockDim.x) {

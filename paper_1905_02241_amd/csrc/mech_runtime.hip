@@ -487,7 +487,6 @@ int launch_plain_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int a
     return MECH_OK;
 }
 
-// `k`: the step, or -1 to take it from the device counter plus kofs (graphs).
 FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, int kofs) {
     FusedArgs a{};
     for (int s = 0; s < (int)c->slots.size(); ++s) a.slot[s] = slot_dev(c, s);
@@ -497,8 +496,8 @@ FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, 
     a.row = 1 + (int)c->slots.size();
     a.tiles = (const int *)(c->buf + c->L.off_tiles) + l.first * a.row;
     a.n_tiles = (int)l.n_tiles;
-    a.kdev = k < 0 ? (const long long *)(c->buf + c->L.off_kdev) : nullptr;
-    a.kbase = k < 0 ? 0 : k;
+    a.kdev = (const long long *)(c->buf + c->L.off_kdev);
+    a.kbase = k;
     a.kofs = kofs;
     a.xcd_order = (l.flags & MECH_LAUNCH_XCD_ORDER) ? 1 : 0;
     a.nontemporal = (l.flags & MECH_LAUNCH_NONTEMPORAL) ? 1 : 0;
@@ -562,7 +561,7 @@ int get_graph(mech_ctx *c, int vmode, double dt, const GlobDev &g, int n, hipGra
     HIPCHK(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
     int rc = MECH_OK;
     for (int j = 0; j < n && rc == MECH_OK; ++j)
-        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, -1, j, c->capture_stream);
+        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, 0, j, c->capture_stream);
     hipError_t e1 = rc == MECH_OK ? launch_bump_k((long long *)(c->buf + c->L.off_kdev), n, c->capture_stream)
                                   : hipSuccess;
     hipGraph_t graph = nullptr;
@@ -627,7 +626,7 @@ int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, 
             k += n;
         }
     }
-    if (use_graph && mids > 0) HIPCHK(c, launch_set_k((long long *)(c->buf + c->L.off_kdev), k, c->stream));
+    if (mids > 0) HIPCHK(c, launch_set_k((long long *)(c->buf + c->L.off_kdev), k, c->stream));
     while (use_graph && mids > 0) {
         const int n = (int)std::min<int64_t>(mids, kGraphSteps);
         hipGraphExec_t exec;
@@ -636,8 +635,8 @@ int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, 
         HIPCHK(c, hipGraphLaunch(exec, c->stream));
         mids -= n;
     }
-    for (; mids > 0; --mids, ++k) {
-        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, k, 0, c->stream);
+    for (int64_t j = 0; j < mids; ++j) {
+        rc = launch_fused_phase(c, kDoState | kDoCur, vmode, g, 0, (int)j, c->stream);
         if (rc) return rc;
     }
     // closing state update at v_{k0+nsteps}
