@@ -183,7 +183,8 @@ __host__ __device__ inline size_t res_node_bytes(int nn, int vmode, bool has_syn
 struct PlainArgs {
     SlotDev slot;
     long long k;
-    int accumulate;            // unused by the state kernel
+    int overwrite;             // identity type: the first of a current update that starts from zero
+    int crossing;              // some node's run crosses a wave's end (k_plain_carry follows)
     int *err;
     GlobDev g;
     NodesDev nd;

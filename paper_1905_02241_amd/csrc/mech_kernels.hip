@@ -642,10 +642,11 @@ __global__ __launch_bounds__(256) void k_plain_cur(PlainArgs a) {
     }
     if (a.slot.identity) {
         // one instance per node: a plain read-modify-write, ordered after the
-        // previous type's kernel on the stream
+        // previous type's kernel on the stream (the first type: a write in
+        // place of clearing the vectors beforehand)
         if (ni >= 0) {
-            a.nd.rhs[ni] -= ci;
-            a.nd.d[ni] += cg;
+            a.nd.rhs[ni] = (a.overwrite ? 0.0 : a.nd.rhs[ni]) - ci;
+            a.nd.d[ni] = (a.overwrite ? 0.0 : a.nd.d[ni]) + cg;
             if (shared) a.nd.ica[ni] += ica;
         }
     } else if (a.atomic_scatter) {
@@ -679,7 +680,7 @@ __global__ __launch_bounds__(256) void k_plain_cur(PlainArgs a) {
                     if (shared) unsafeAtomicAdd(&a.nd.ica[ni], z);
                 }
             }
-            if (lane == 0 && !cont) a.carry_node[c] = -1;
+            if (a.crossing && lane == 0 && !cont) a.carry_node[c] = -1;
         }
     }
     if (flag) atomicOr(a.err, 1);
@@ -2437,7 +2438,7 @@ static hipError_t cur_t(const PlainArgs &a, hipStream_t s) {
 hipError_t launch_plain_cur(bool fp32, const PlainArgs &a, hipStream_t s) {
     if (a.slot.n == 0) return hipSuccess;
     const hipError_t e = fp32 ? cur_t<float>(a, s) : cur_t<double>(a, s);
-    if (e != hipSuccess || a.slot.identity || a.atomic_scatter) return e;
+    if (e != hipSuccess || a.slot.identity || a.atomic_scatter || !a.crossing) return e;
     const int n_chunks = (a.slot.n + 63) / 64;
     k_plain_carry<<<blocks(n_chunks, 256), 256, 0, s>>>(a, n_chunks, a.g.shared_ca ? 1 : 0);
     return hipGetLastError();

@@ -81,6 +81,7 @@ struct SlotHost {
     int64_t n = 0, np = 0;
     bool identity = false;
     bool perm_identity = true;
+    bool crossing = false;         // a node's run crosses a multiple of 64 instances (kPad, a wave)
     std::vector<int32_t> perm;     // internal -> caller index (empty when identity)
     std::vector<int32_t> ni;       // node index, internal (sorted) order
     size_t off_ni = 0, off_gid = 0, off_ica = 0;
@@ -467,16 +468,18 @@ int upload_var(mech_ctx *c, int slot, size_t off, bool is_double, const double *
 int launch_plain_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int accumulate) {
     PlainArgs a{};
     a.k = k;
-    a.accumulate = accumulate;
     a.err = (int *)(c->buf + c->L.off_err);
     a.g = g;
     a.nd = c->nd;
     a.atomic_scatter = (c->set.flags & MECH_LAUNCH_PLAIN_ATOMIC) ? 1 : 0;
-    if (cur && !accumulate) HIPCHK(c, launch_fill(c->nd.rhs, c->nd.d, (int)c->n_nodes, c->stream));
+    const bool starts = cur && !accumulate && !c->slots.empty() && c->slots[0].identity && c->slots[0].n > 0;
+    if (cur && !accumulate && !starts) HIPCHK(c, launch_fill(c->nd.rhs, c->nd.d, (int)c->n_nodes, c->stream));
     if (cur && !accumulate && g.shared_ca) HIPCHK(c, launch_fill(c->nd.ica, c->nd.ica, (int)c->n_nodes, c->stream));
     for (int s = 0; s < (int)c->slots.size(); ++s) {
         a.slot = slot_dev(c, s);
         const SlotHost &h = c->slots[s];
+        a.overwrite = starts && s == 0;
+        a.crossing = h.crossing;
         a.carry_node = (int *)(c->buf + h.off_carry);
         a.carry_val = (double *)(c->buf + h.off_carry + align_up(4 * ((size_t)h.np / kPad)));
         if (cur) HIPCHK(c, launch_plain_cur(c->fp32, a, c->stream));
@@ -839,6 +842,8 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
             }
         }
     }
+    for (SlotHost &h : c->slots)
+        for (int64_t i = kPad; i < h.n && !h.crossing; i += kPad) h.crossing = h.ni[i] == h.ni[i - 1];
     {
         // the fused paths sum a node's contributions in fixed point, exact up
         // to kMaxPerNode of them
