@@ -1477,6 +1477,17 @@ __device__ __forceinline__ void tile_add(int j, double ci, double cg, const doub
     }
 }
 
+// The globals of a kernel whose first argument is FusedArgs, read from the
+// argument segment where they are used.  The compiler otherwise loads all of
+// them once, runs out of scalar registers over the eight types' code and keeps
+// the rest in lanes of vector registers, from where every use is a vector
+// instruction.
+__device__ __forceinline__ const GlobDev &arg_globals() {
+    auto p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(FusedArgs, g);
+    asm volatile("" : "+s"(p));
+    return *(const GlobDev *)p;
+}
+
 // Instance i of a slot within a tile whose nodes start at nlo.
 template <class S, int KIND, int PH, bool NT, bool EXT>
 __device__ __forceinline__ void tile_one(const SlotDev &sl, int i, int nlo, const double *vl, const double *sc,
@@ -1532,16 +1543,16 @@ __device__ __forceinline__ int tile_of(int b, int T, int xcd_order) {
             const int lo = r0[1 + s], hi = r1[1 + s]; \
             switch (sl.kind) { \
             case MECH_PAS: \
-                if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); \
+                if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
                 break; \
-            case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
-            case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
-            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
-            case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
-            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
-            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break; \
+            case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
             case MECH_CABUF: \
-                if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); \
+                if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
                 break; \
             default: break; \
             } \
@@ -1954,10 +1965,10 @@ __device__ __forceinline__ void res_pass(const FusedArgs &a, const int *r0, cons
         char *p = inst + o;
         switch (kind) {
 #define MECH_RES_CASE(K)                                                                                   \
-    case K: tile_one<S, K, PH, false, EXT>(res_carve<S>(K, n, p), i, 0, vl, sc, ar, ad, cl, ai, a.g, k, ion, flag); break;
+    case K: tile_one<S, K, PH, false, EXT>(res_carve<S>(K, n, p), i, 0, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break;
         case MECH_PAS:
             if (PH & kDoCur)
-                tile_one<S, MECH_PAS, PH, false, EXT>(res_carve<S>(MECH_PAS, n, p), i, 0, vl, sc, ar, ad, cl, ai, a.g, k,
+                tile_one<S, MECH_PAS, PH, false, EXT>(res_carve<S>(MECH_PAS, n, p), i, 0, vl, sc, ar, ad, cl, ai, arg_globals(), k,
                                                       ion, flag);
             break;
         MECH_RES_CASE(MECH_HH)
@@ -1970,7 +1981,7 @@ __device__ __forceinline__ void res_pass(const FusedArgs &a, const int *r0, cons
         case MECH_CABUF:
             if constexpr (EXT)
                 tile_one<S, MECH_CABUF, PH, false, EXT>(res_carve<S>(MECH_CABUF, n, p), i, 0, vl, sc, ar, ad, cl, ai,
-                                                        a.g, k, ion, flag);
+                                                        arg_globals(), k, ion, flag);
             break;
         default: break;
         }
