@@ -60,23 +60,7 @@ __device__ __forceinline__ float one_minus_exp_f(float z) {
 }
 
 // ------------------------------------------------------------ FP64 math --
-// a/b within about one ulp without the IEEE division sequence's scaling
-// steps: the hardware reciprocal, two Newton-Raphson refinements
-// r <- r + r (1 - b r), then one residual correction of the quotient.  Valid
-// for normal, finite, non-zero b and a/b in the normal range, which holds
-// for every rate expression it is used on.
-__device__ __forceinline__ double rcp_d(double b) {
-    double r = __builtin_amdgcn_rcp(b);
-    r = fma(fma(-b, r, 1.0), r, r);
-    return fma(fma(-b, r, 1.0), r, r);
-}
-__device__ __forceinline__ double fdiv(double a, double b) {
-    const double r = rcp_d(b);
-    const double q = a * r;
-    return fma(fma(-b, q, a), r, q);
-}
-
-// exp_d, expm1_d, log_d and sin_d: mech_math.h.
+// rcp_d, fdiv, exp_d, expm1_d, log_d and sin_d: mech_math.h.
 
 // a x/(1 - exp(-x/k)), with the limit a k at x = 0; em1 = expm1(-x/k) is
 // returned so that a caller can reuse exp(-x/k) = em1 + 1.
@@ -89,10 +73,11 @@ __device__ __forceinline__ double linexp_d(double a, double inv_k, double x, dou
     return linexp_d(a, inv_k, x, lim, em1);
 }
 
-// cnexp factor e^{-y} over one step, or its (1,1) Pade approximant
+// cnexp factor e^{-y} over one step (a rate that is not a number makes the
+// gate's target one as well), or its (1,1) Pade approximant
 // (1 - y/2)/(1 + y/2) (the optional replacement of the paper's section 5.2).
 __device__ __forceinline__ double cnexp_factor(double y, int pade) {
-    return pade ? fdiv(1.0 - 0.5 * y, 1.0 + 0.5 * y) : exp_d(-y);
+    return pade ? fdiv(1.0 - 0.5 * y, 1.0 + 0.5 * y) : exp_decay_d(-y);
 }
 // 1 - factor in FP32 without cancellation: the series / exp form above, or
 // y/(1 + y/2) for the Pade approximant.

@@ -16,7 +16,8 @@ namespace mech {
 // about forty vector registers across the fused kernels' loops, which held
 // the FP64 fused kernel at 4 waves per SIMD; these take each coefficient as
 // the scalar operand of the fused multiply-add (fma_s), so the kernels fit
-// in 79 (FP64) and 71 (FP32-mixed) registers.
+// in 70 to 80 (FP64) and 55 (FP32-mixed) registers.
+
 // a b + c with c in a scalar register pair (one scalar operand is allowed per
 // vector instruction).
 MECH_HD_INLINE double fma_s(double a, double b, double c) {
@@ -28,32 +29,52 @@ MECH_HD_INLINE double fma_s(double a, double b, double c) {
     return fma(a, b, c);   // host builds (the accuracy test): the same operation
 #endif
 }
+// 1/b within about one ulp without the IEEE division sequence's scaling steps:
+// the hardware reciprocal (2^-24.3 measured) and one third-order step, r <- r +
+// r (e + e^2) with e = 1 - b r, whose error is e^3 (two Newton steps, which
+// this replaces, take one operation more and end at the same rounding error).
+// Valid for normal, finite, non-zero b.
+MECH_HD_INLINE double rcp_d(double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double r = __builtin_amdgcn_rcp(b), e = fma(-b, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+#else
+    return 1.0 / b;
+#endif
+}
+// a/b with one residual correction of the quotient, for a/b in the normal
+// range (every rate expression's).
+MECH_HD_INLINE double fdiv(double a, double b) {
+    const double r = rcp_d(b);
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+
 // Reduction after Cody and Waite: x = k ln2 + r with k = rint(x / ln2) and r
 // formed by two fused multiply-adds against ln2 split into a double and its
-// remainder, so |r| <= ln2/2 up to rounding.  e^r - 1 is its Taylor series
-// to r^13/13!, whose tail stays below 2^-55 relative to r.  x is first
-// clamped to [-746, 710], beyond which e^x is 0 or +inf anyway (NaN passes
-// unchanged).  Against long-double references (tests/test_math_accuracy.py):
-// e^x within 1 ulp, e^x - 1 within 1.8 ulp, ln x within 1.2 ulp, sin x within
-// 1.5 ulp.
+// remainder, so |r| <= ln2/2 up to rounding.  e^r - 1 = r + r^2/2 + r^3 p(r)
+// with p the polynomial of degree 9 whose error relative to e^r - 1 is smallest
+// there (Remez exchange in 200 bits: 2^-61.7; degree 8 would be 2^-55.2, which
+// shows in the result).  For |x| < 2^50; far below -745 and above 710 the
+// exponent adjust alone gives 0 and +inf, and NaN passes.  Against long-double
+// references (tests/test_math_accuracy.py): e^x within 1 ulp,
+// e^x - 1 within 1.8 ulp, ln x within 1.2 ulp, sin x within 1.5 ulp.
 constexpr double kLn2Hi = 0x1.62e42fefa39efp-1, kLn2Lo = 0x1.abc9e3b39803fp-56, kLog2e = 0x1.71547652b82fep+0;
 MECH_HD_INLINE double em1_series(double r) {
-    double p = 1.0 / 6227020800.0;   // 1/13!, then 1/12! ... 1/3!
-    p = fma_s(p, r, 1.0 / 479001600.0);
-    p = fma_s(p, r, 1.0 / 39916800.0);
-    p = fma_s(p, r, 1.0 / 3628800.0);
-    p = fma_s(p, r, 1.0 / 362880.0);
-    p = fma_s(p, r, 1.0 / 40320.0);
-    p = fma_s(p, r, 1.0 / 5040.0);
-    p = fma_s(p, r, 1.0 / 720.0);
-    p = fma_s(p, r, 1.0 / 120.0);
-    p = fma_s(p, r, 1.0 / 24.0);
-    p = fma_s(p, r, 1.0 / 6.0);
+    double p = 0x1.1ef5222fa41b6p-29;
+    p = fma_s(p, r, 0x1.af5d200d2370ep-26);
+    p = fma_s(p, r, 0x1.27e52b2d06e95p-22);
+    p = fma_s(p, r, 0x1.71ddf95400f23p-19);
+    p = fma_s(p, r, 0x1.a01a018305ca2p-16);
+    p = fma_s(p, r, 0x1.a01a01af758adp-13);
+    p = fma_s(p, r, 0x1.6c16c16c1cce4p-10);
+    p = fma_s(p, r, 0x1.111111110f7ecp-7);
+    p = fma_s(p, r, 0x1.5555555555549p-5);
+    p = fma_s(p, r, 0x1.5555555555559p-3);
     p = fma(p, r, 0.5);
     return fma(r * r, p, r);
 }
 MECH_HD_INLINE int exp_reduce(double x, double &r) {
-    x = x < -746.0 ? -746.0 : (x > 710.0 ? 710.0 : x);
     const double k = rint(x * kLog2e);
     r = fma(-k, kLn2Lo, fma(-k, kLn2Hi, x));
     return (int)k;
@@ -63,11 +84,16 @@ MECH_HD_INLINE double exp_d(double x) {
     const int k = exp_reduce(x, r);
     return ldexp(1.0 + em1_series(r), k);
 }
+// e^x for x <= 0 of any size (-inf too), for a decay over a step: 0 below -745.
+// NaN gives 0 as well: the caller's other operand carries it.
+MECH_HD_INLINE double exp_decay_d(double x) { return exp_d(fmax(x, -746.0)); }
 // e^x - 1 = 2^k (e^r - 1) + (2^k - 1): the series alone when k = 0, so the
-// result keeps its relative accuracy near x = 0.
+// result keeps its relative accuracy near x = 0; k at most 1024, where 2^k is
+// +inf and the series' part still finite.
 MECH_HD_INLINE double expm1_d(double x) {
     double r;
-    const int k = exp_reduce(x, r);
+    int k = exp_reduce(x, r);
+    k = k < 1024 ? k : 1024;
     return ldexp(em1_series(r), k) + (ldexp(1.0, k) - 1.0);
 }
 // ln x = e ln2 + ln m with x = m 2^e, m in [sqrt(1/2), sqrt(2)).  With
@@ -84,7 +110,7 @@ MECH_HD_INLINE double log_d(double x) {
         e -= 1;
     }
     const double f = m - 1.0;
-    const double s = f / (m + 1.0), z = s * s;
+    const double s = fdiv(f, m + 1.0), z = s * s;
     double p = 2.0 / 23.0;            // then 2/21 ... 2/5
     p = fma_s(p, z, 2.0 / 21.0);
     p = fma_s(p, z, 2.0 / 19.0);
