@@ -392,20 +392,23 @@ int upload_tiles(mech_ctx *c, Launch &l, size_t first) {
 // The batched path's shape for a context whose caller has not chosen one:
 // 256 threads, and tiles that keep every CU busy and grow with the work, so
 // that a thread takes one instance where latency counts and eight where
-// streaming does.  A tile spans at most 640 nodes (30 KiB of LDS, five
-// workgroups a CU).  us per step at this tile / at the default's 2048
-// instances, by instances per CU (256 of them):
-//     39 (hh)      5.6 / 12.0      1291 (cells, five types) 13.8 / 17.2
-//     391 (hh)     7.4 / 12.8      3908 (C5's mix)          23.2 / 26.6
-//     781 (hh+pas) 7.9 / 14.1      7813 (hh+pas, 640 nodes) 33.6 / 37.8
-// and at 5988 (cells) 2048 instances 27.4, 1024 29.2.
+// streaming does.  A tile spans at most 448 nodes: 21.5 KiB of LDS, so that the
+// seven workgroups that a CU's registers hold (70 VGPRs) fit its LDS too.  us
+// per step, by instances per CU (256 of them):
+//     39 (hh)           256 instances a tile 5.6,  2048 12.0
+//     781 (hh+pas)      512  7.9,  2048 14.1
+//     1291 (five types) 512 12.2,  1024 13.2
+//     5988 (five types) 1024 21.9, 2048 23.6
+//     7813 (synapses)   1024 29.3, 2048 28.3
+//     32553 (C5's mix)  2048 and 448 nodes 130.2, 640 nodes 140.1; FP32 88.2, 96.1
+//     7813 (hh+pas)     448 nodes 29.1, 640 32.7; FP32 22.2, 25.3
 Launch fit_launch(const mech_ctx *c) {
     Launch l;
     int64_t total = 0;
     for (const auto &h : c->slots) total += h.n;
     const int64_t w = total / c->n_cu;
-    l.budget = w < 512 ? 256 : w < 2048 ? 512 : w < 5000 ? 1024 : 2048;
-    l.nodes = std::min(l.budget, 640);
+    l.budget = w < 512 ? 256 : w < 2048 ? 512 : w < 7000 ? 1024 : 2048;
+    l.nodes = std::min(l.budget, 448);
     return l;
 }
 

@@ -21,10 +21,10 @@ def same(a, b):
 
 
 # instances: a context of one node (no room for a second tile table) and of
-# two, both sides of the tile size's thresholds (512, 2048 and 5000 instances
+# two, both sides of the tile size's thresholds (512, 2048 and 7000 instances
 # per CU of 256), and a ragged mix of types
 @pytest.mark.parametrize("make,n", [("hh", 1), ("hh", 2), ("hh", 131071), ("hh", 131072), ("hh", 524287),
-                                    ("hh", 524288), ("hh", 1280001), ("mixed", 1), ("mixed", 4097), ("mixed", 39500)])
+                                    ("hh", 524288), ("hh", 1791999), ("hh", 1792000), ("mixed", 1), ("mixed", 4097), ("mixed", 39500)])
 def test_own_shape_gives_the_same_bits(make, n):
     w = W.make_c1(n_nodes=n) if make == "hh" else W.make_c5(n_nodes=n)
     steps = 5
