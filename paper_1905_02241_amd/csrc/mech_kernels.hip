@@ -1399,11 +1399,11 @@ hipError_t cable_allow_lds(size_t bytes) {
 // M = 1.5 * 2^52 to y (|y| < 2^51) leaves round(y) in the low bits of the
 // sum, and y - ((y + M) - M) is the exact remainder.  With at most 2^19
 // contributions per node neither word's sum can overflow, so no carry is
-// needed while adding; the flush combines the words into the 128-bit total
-// and rounds it to FP64 once.  A larger or non-finite contribution raises
-// the kernel's error flag (its words are then meaningless, and the step is
-// reported as failed at the next mech_sync).  The host rejects workloads
-// with more instances on one node (kMaxPerNode).
+// needed while adding; the flush combines the words and rounds to FP64 once.
+// A larger or non-finite contribution raises the kernel's error flag (its
+// words are then meaningless, and the step is reported as failed at the next
+// mech_sync).  The host rejects workloads with more instances on one node
+// (kMaxPerNode).
 struct Acc {
     unsigned long long *lo, *hi;
 };
@@ -1426,22 +1426,12 @@ __device__ __forceinline__ void fx_add(Acc a, int j, double x, int &flag) {
     atomicAdd(a.hi + j, (unsigned long long)h);
     atomicAdd(a.lo + j, (unsigned long long)l);
 }
-// The total H 2^44 + L (the two words' signed sums) as a 128-bit two's
-// complement pair, then its magnitude's two words converted separately and
-// added (nothing cancels; within one rounding of the exact total), and the
-// sign applied.
+// The total (H 2^44 + L) 2^-67 of the two words' signed sums: both convert to
+// FP64 exactly below 2^53 (H: a node's |x| adding up to less than 2^30; L: at
+// most 2^10 contributions; beyond that each within one rounding of itself),
+// and the fused multiply-add rounds their sum once.
 __device__ __forceinline__ double fx_get(Acc a, int j) {
-    const long long H = (long long)a.hi[j], L = (long long)a.lo[j];
-    const unsigned long long sh = (unsigned long long)H << 44;
-    unsigned long long lo = sh + (unsigned long long)L;
-    unsigned long long hi = (unsigned long long)((H >> 20) + (L >> 63)) + (lo < sh ? 1ull : 0ull);
-    const bool neg = (long long)hi < 0;
-    if (neg) {   // two's complement negation of the pair
-        lo = ~lo + 1ull;
-        hi = ~hi + (lo == 0ull ? 1ull : 0ull);
-    }
-    const double m = (double)hi * 0x1p-3 + (double)lo * 0x1p-67;
-    return neg ? -m : m;
+    return fma((double)(long long)a.lo[j], 0x1p-67, (double)(long long)a.hi[j] * 0x1p-23);
 }
 
 // LDS per tile node: v and 100/area (two doubles), the rhs and d
