@@ -130,6 +130,7 @@ struct ResArgs {
     int nsub;                  // current updates (steps) in this launch
     int first_state;           // state update of step k0-1 before the first current update
     int last_state;            // state update at v_{k0+nsub} after the last one
+    int table;                 // LDS offset of the table of runs by position, 0 without room for it
 };
 
 // The arrays of a mechanism kind as the time-fused path stages them: STATEs,
@@ -172,7 +173,8 @@ __host__ __device__ inline size_t res_slot_bytes(int kind, int n, int ss) {
 // each), 100/area (point processes), 1e-3 cm/dt (isolated) or the four clamp
 // waveform parameters, and the shared calcium ion's cai and ica accumulator
 // (two words); then an int spike counter per node and a 16-byte aligned
-// table: 16 bytes per slot and 32 bytes of run ends.
+// table: 16 bytes per slot and 32 bytes of run ends (a table of runs by position
+// follows the slots' arrays where the LDS has room for it).
 __host__ __device__ inline int res_node_doubles(int vmode, bool has_syn, bool ion) {
     return 5 + (has_syn ? 1 : 0) + (vmode == MECH_V_CLAMP ? 4 : 1) + (ion ? 3 : 0);
 }

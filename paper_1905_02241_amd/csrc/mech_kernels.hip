@@ -1911,28 +1911,29 @@ __device__ __forceinline__ void res_copy(const SlotDev &g, const SlotDev &l, int
 // The slots' runs are laid end to end, each padded to a whole wave, and the
 // block's threads stride over that sequence: every thread gets an equal
 // share whatever the mix of types, and every wave works on one type.  A wave
-// finds its run by comparing its first position with the runs' ends and
-// reads the run's start, LDS offset, count and kind from a table the tile
-// keeps in LDS (ends included: scalar registers are the scarce resource
-// here, and every value kept in them across the loop is spilled and
-// reloaded with VALU instructions).  Measured against the alternatives on
-// the 100 M-instance workload, FP64 / FP32 ms per step: this 1.08 / 0.53;
-// the ends in scalar registers 1.26 / 0.62; rescanning the slots per wave
-// from the tile table in memory 1.42 / 0.93; the whole table in scalar
-// registers 1.52 / 0.81.
+// reads its run's start, LDS offset, count and kind from a table in LDS with
+// an entry for every 64 positions (`blk`), or, where a tile leaves no room
+// for that, finds its run by comparing its position with the runs' ends and
+// takes the run's entry (`tab`; the ends as well from LDS: scalar registers
+// are the scarce resource here, and every value kept in them across the loop
+// is spilled and reloaded with VALU instructions).
+// us per 64 steps, by the runs' ends and by the table: 1 M nodes hh+pas FP32
+// 711 and 658, FP64 1041 and 989; 1 M of C5's mix FP32 478 and 436, FP64 726
+// and 690 (the ends in scalar registers, or the tile table in memory, were
+// slower still).
+__device__ __forceinline__ int4 res_run(const int4 *tab, int g) {
+    const int4 e0 = tab[kMaxSlots], e1 = tab[kMaxSlots + 1];
+    return tab[(g >= e0.x) + (g >= e0.y) + (g >= e0.z) + (g >= e0.w) + (g >= e1.x) + (g >= e1.y) + (g >= e1.z)];
+}
 template <class S, int PH, bool EXT>
-__device__ __forceinline__ void res_pass(const FusedArgs &a, const int *r0, const int *r1, const int4 *tab, char *inst,
+__device__ __forceinline__ void res_pass(const int4 *tab, const int4 *blk, char *inst,
                                          const double *vl, const double *sc, Acc ar, Acc ad, const double *cl,
                                          Acc ai, long long k, bool ion, int &flag) {
-    const int4 *ends = tab + kMaxSlots;
-    const int total = __builtin_amdgcn_readfirstlane(ends[1].w);
+    const int total = __builtin_amdgcn_readfirstlane(tab[kMaxSlots + 1].w);
     const int lane = (int)(threadIdx.x & 63);
     for (int g0 = (int)threadIdx.x - lane; g0 < total; g0 += (int)blockDim.x) {
         const int gw = __builtin_amdgcn_readfirstlane(g0);
-        const int4 e0 = ends[0], e1 = ends[1];
-        const int s = (gw >= e0.x) + (gw >= e0.y) + (gw >= e0.z) + (gw >= e0.w) + (gw >= e1.x) + (gw >= e1.y) +
-                      (gw >= e1.z);
-        const int4 t = tab[__builtin_amdgcn_readfirstlane(s)];
+        const int4 t = blk ? blk[gw >> 6] : res_run(tab, gw);
         const int base = __builtin_amdgcn_readfirstlane(t.x), o = __builtin_amdgcn_readfirstlane(t.y);
         const int n = __builtin_amdgcn_readfirstlane(t.z), kind = __builtin_amdgcn_readfirstlane(t.w);
         const int i = gw - base + lane;
@@ -2035,12 +2036,18 @@ __global__ __launch_bounds__(1024) void k_resident(FusedArgs a, ResArgs r) {
             }
         }
         __syncthreads();
+        int4 *blk = r.table ? (int4 *)((char *)lds + r.table) : nullptr;
+        if (blk) {
+            const int total = tab[kMaxSlots + 1].w;
+            for (int q = threadIdx.x; q < total >> 6; q += blockDim.x) blk[q] = res_run(tab, q << 6);
+            __syncthreads();
+        }
         for (int sub = 0; sub < r.nsub; ++sub) {
             const long long k = r.k0 + sub;
             if (sub == 0 && !r.first_state)
-                res_pass<S, kDoCur, EXT>(a, r0, r1, tab, inst, vl, sc, ar, ad, cl, ai, k, ion, flag);
+                res_pass<S, kDoCur, EXT>(tab, blk, inst, vl, sc, ar, ad, cl, ai, k, ion, flag);
             else
-                res_pass<S, kDoCur | kDoState, EXT>(a, r0, r1, tab, inst, vl, sc, ar, ad, cl, ai, k, ion, flag);
+                res_pass<S, kDoCur | kDoState, EXT>(tab, blk, inst, vl, sc, ar, ad, cl, ai, k, ion, flag);
             __syncthreads();
             // flush: the same voltage provision as k_fused's, from LDS
             const bool last = sub + 1 == r.nsub;
@@ -2080,7 +2087,7 @@ __global__ __launch_bounds__(1024) void k_resident(FusedArgs a, ResArgs r) {
             __syncthreads();
         }
         if (r.last_state) {
-            res_pass<S, kDoState, EXT>(a, r0, r1, tab, inst, vl, sc, ar, ad, cl, ai, r.k0 + r.nsub, ion, flag);
+            res_pass<S, kDoState, EXT>(tab, blk, inst, vl, sc, ar, ad, cl, ai, r.k0 + r.nsub, ion, flag);
             __syncthreads();
         }
         {

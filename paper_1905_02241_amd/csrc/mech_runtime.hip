@@ -221,7 +221,7 @@ struct mech_ctx {
     size_t res_lds_allowed = 0;
     // largest tile's LDS on that path per (voltage mode, shared ion), for the
     // current tile table (cleared when the table is rebuilt)
-    std::map<std::pair<int, int>, size_t> res_lds_cache;
+    std::map<std::pair<int, int>, std::pair<size_t, size_t>> res_lds_cache;
     // graphs of 1..kGraphSteps fused steps, keyed by (vmode, dt, steps)
     std::map<std::tuple<int, uint64_t, int>, hipGraphExec_t> graphs;
     std::string err;
@@ -665,21 +665,26 @@ int res_check_shapes(mech_ctx *c) {
     return MECH_OK;
 }
 
-// Dynamic LDS of the largest tile of the current table.
-size_t res_lds_need(mech_ctx *c, int vmode, bool ion) {
+// Dynamic LDS of the largest tile of the current table, and the most entries
+// (one for every 64 positions) that a tile's table of runs by position has.
+std::pair<size_t, size_t> res_lds_need(mech_ctx *c, int vmode, bool ion) {
     const auto key = std::make_pair(vmode, ion ? 1 : 0);
     const auto hit = c->res_lds_cache.find(key);
     if (hit != c->res_lds_cache.end()) return hit->second;
     const int ns = (int)c->slots.size(), row = 1 + ns, ss = c->fp32 ? 4 : 8;
-    size_t need = 0;
+    size_t need = 0, blocks = 0;
     for (int64_t t = 0; t < c->set.n_tiles; ++t) {
         const int32_t *r0 = c->set.rows.data() + (size_t)t * row, *r1 = r0 + row;
-        size_t b = res_node_bytes(r1[0] - r0[0], vmode, c->has_syn, ion);
-        for (int s = 0; s < ns; ++s) b += res_slot_bytes(c->slots[s].kind, r1[1 + s] - r0[1 + s], ss);
+        size_t b = res_node_bytes(r1[0] - r0[0], vmode, c->has_syn, ion), e = 0;
+        for (int s = 0; s < ns; ++s) {
+            const int n = r1[1 + s] - r0[1 + s];
+            b += res_slot_bytes(c->slots[s].kind, n, ss);
+            e += ((size_t)n + 63) / 64;
+        }
         need = std::max(need, b);
+        blocks = std::max(blocks, e);
     }
-    c->res_lds_cache[key] = need;
-    return need;
+    return c->res_lds_cache[key] = {need, blocks};
 }
 
 size_t device_lds_bytes() {
@@ -699,17 +704,23 @@ int step_resident(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode)
     if (rc) return rc;
     const GlobDev g = make_glob(c, dt);
     ResArgs r{};
-    const size_t need = res_lds_need(c, vmode, g.shared_ca != 0), cap = device_lds_bytes();
+    const auto [need, blocks] = res_lds_need(c, vmode, g.shared_ca != 0);
+    const size_t cap = device_lds_bytes();
     if (need > cap)
         return fail(c, MECH_ERR_STATE,
                     "a tile needs %zu B of LDS on the time-fused path, the device allows %zu: lower "
                     "tile_instances or tile_nodes (mech_set_launch)",
                     need, cap);
-    if (need > c->res_lds_allowed) {
+    if (cap > c->res_lds_allowed) {
         HIPCHK(c, resident_allow_lds(cap));
         c->res_lds_allowed = cap;
     }
     if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
+    // the table of runs by position, where it does not cost a CU a workgroup
+    const size_t table = (need + 15) & ~(size_t)15, with = table + 16 * blocks;
+    const bool fits = with <= cap && (need == 0 || cap / with == cap / need);
+    r.table = fits ? (int)table : 0;
+    const size_t lds = fits ? with : need;
     const FusedArgs a = fused_args(c, c->set, g, 0, 0);
     for (int64_t done = 0; done < nsteps;) {
         const int n = (int)std::min<int64_t>(c->res_steps, nsteps - done);
@@ -717,7 +728,7 @@ int step_resident(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode)
         r.nsub = n;
         r.first_state = done > 0 ? 1 : 0;
         r.last_state = done + n == nsteps ? 1 : 0;
-        HIPCHK(c, launch_resident(c->fp32, vmode, a, r, fused_grid(c, c->set), c->set.block, need, c->stream));
+        HIPCHK(c, launch_resident(c->fp32, vmode, a, r, fused_grid(c, c->set), c->set.block, lds, c->stream));
         done += n;
     }
     return MECH_OK;
@@ -1434,7 +1445,7 @@ static int autotune_impl(mech_ctx *c, double dt, int vmode, int nsteps, int reps
         t = 1e300;
         int q = mech_set_launch(c, sh.block, sh.budget, sh.nodes, sh.bpc, sh.flags);
         if (q) return q;
-        if (resident && res_lds_need(c, vmode, ion_on) > cap) return MECH_OK;
+        if (resident && res_lds_need(c, vmode, ion_on).first > cap) return MECH_OK;
         auto run = [&](int m, int64_t k0) {
             return resident ? step_resident(c, m, k0, dt, vmode) : step_batched(c, m, k0, dt, vmode, false);
         };

@@ -108,3 +108,17 @@ def test_single_phases_match_the_oracle(name, shared_ca):
         b = m.nodes()
         for key in ("rhs", "d"):
             assert np.array_equal(b[key], 2.0 * a[key]), key
+
+
+def test_resident_tile_without_room_for_the_table_of_runs():
+    """A tile that fills the LDS of a workgroup to within the 2 KiB that the
+    table would take: its waves find their runs by the ends."""
+    n = 8150
+    w = W.make_tiny(87, kinds=("pas",), n_nodes=1, vmode="isolated")
+    rng = np.random.default_rng(87)
+    w.slots[0] = W.Slot("pas", np.zeros(n, dtype=np.int32),
+                        {"g": rng.uniform(1e-7, 2e-7, n), "e": rng.uniform(-80.0, -60.0, n)})
+    shape = (1024, 16384, 64, 0, 1)
+    a, _ = run_gpu(w, 20, "batched", "fp64", launch=shape)
+    b, _ = run_gpu(w, 20, "resident", "fp64", launch=shape, resident_steps=6)
+    same(a, b)
