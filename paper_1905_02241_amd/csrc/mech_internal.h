@@ -220,7 +220,8 @@ hipError_t launch_phase_cur(bool fp32, const FusedArgs &a, int accumulate, int t
                             hipStream_t s);
 hipError_t launch_phase_state(bool fp32, const FusedArgs &a, hipStream_t s);
 size_t phase_lds_bytes(int tile_nodes, int tile_instances, int n_slots, bool ion);
-hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int block, int tile_nodes, hipStream_t s);
+hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int first, int last, int block,
+                        int tile_nodes, hipStream_t s);
 size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion);
 hipError_t fused_allow_lds(size_t bytes);
 hipError_t launch_resident(bool fp32, int vmode, const FusedArgs &a, const ResArgs &r, int grid, int block,

@@ -1508,9 +1508,11 @@ __device__ __forceinline__ int tile_of(int b, int T, int xcd_order) {
     return x * q + min(x, r) + j;
 }
 
-// Every instance of a tile.  A macro: as a function taking the arguments by
-// reference it cost the FP32 kernel 3 VGPRs and the FP64 one 8 % of its speed.
-#define MECH_TILE_PASS() \
+// Every instance of a tile in the phases PH, dealt to the waves as in a pass of
+// the phases DEAL (one without a current update leaves pas out).  A macro: as a
+// function taking the arguments by reference it cost the FP32 kernel 3 VGPRs
+// and the FP64 one 8 % of its speed.
+#define MECH_TILE_PASS(PH, DEAL) \
     do { \
         int first = 0; \
         for (int s = 0; s < a.n_slots; ++s) { \
@@ -1518,20 +1520,20 @@ __device__ __forceinline__ int tile_of(int b, int T, int xcd_order) {
             const int lo = r0[1 + s], hi = r1[1 + s]; \
             switch (sl.kind) { \
             case MECH_PAS: \
-                if (PH & kDoCur) tile_slot<S, MECH_PAS, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
+                if ((PH) & kDoCur) tile_slot<S, MECH_PAS, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
                 break; \
-            case MECH_HH: tile_slot<S, MECH_HH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
-            case MECH_IH: tile_slot<S, MECH_IH, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
-            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
-            case MECH_SYN: tile_slot<S, MECH_SYN, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
-            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
-            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_HH: tile_slot<S, MECH_HH, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_IH: tile_slot<S, MECH_IH, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_CAHVA: tile_slot<S, MECH_CAHVA, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_SYN: tile_slot<S, MECH_SYN, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_KMARKOV: tile_slot<S, MECH_KMARKOV, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
+            case MECH_CAPUMP: tile_slot<S, MECH_CAPUMP, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); break; \
             case MECH_CABUF: \
-                if constexpr (EXT) tile_slot<S, MECH_CABUF, PH, NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
+                if constexpr (EXT) tile_slot<S, MECH_CABUF, (PH), NT, EXT>(sl, lo, hi, first, nlo, vl, sc, ar, ad, cl, ai, arg_globals(), k, ion, flag); \
                 break; \
             default: break; \
             } \
-            if (!(sl.kind == MECH_PAS && !(PH & kDoCur))) first += (hi - lo + 63) & ~63; \
+            if (!(sl.kind == MECH_PAS && !((DEAL) & kDoCur))) first += (hi - lo + 63) & ~63; \
             while (first >= (int)blockDim.x) first -= (int)blockDim.x; \
         } \
     } while (0)
@@ -1569,7 +1571,7 @@ __global__ __launch_bounds__(1024) void k_fused(FusedArgs a, int tn) {
             }
         }
         __syncthreads();
-        MECH_TILE_PASS();
+        MECH_TILE_PASS(PH, PH);
         if (PH & kDoCur) {
             __syncthreads();
             for (int j = threadIdx.x; j < nn; j += blockDim.x) {
@@ -1735,19 +1737,23 @@ __global__ __launch_bounds__(256) void k_phase_state(FusedArgs a) {
 }
 
 // -------------------------------------------------- several steps a launch --
-// A tile's middle steps in one launch, for contexts whose instance arrays stay
-// in the L2s from one step to the next: launches and the reading of the tile's
-// nodes, not the arrays, are then most of a step.  Each step is k_fused's,
-// STATEs are loaded and stored in every one of them (always by the same
-// thread, so that no step waits for another's stores to be visible), the
-// tile's node data stays in LDS, and rhs, d, v, spikes and the node ion are
-// written after the last step.  Clamp and isolated modes, whose tiles do not
-// depend on each other.
-// us per step, a launch each (from graphs) / 256 a launch: 10 k hh 5.4 / 2.9,
-// 67 k hh+pas in FP32 6.3 / 2.4, 67 k of C5's mix in FP32 7.1 / 3.3, 15 k of
-// eight types 11.7 / 9.5, 266 k synapses 8.6 / 5.5.
+// A tile's steps in one launch, for contexts whose instance arrays stay in the
+// L2s from one step to the next: launches and the reading of the tile's nodes,
+// not the arrays, are then most of a step.  Each step is k_fused's, STATEs are
+// loaded and stored in every one of them (always by the same thread, so that
+// no step waits for another's stores to be visible), the tile's node data
+// stays in LDS, and rhs, d, v, spikes and the node ion are written after the
+// last step.  A call's first pass (current update alone, from the clamp's
+// value in clamp mode) and its last (state update alone) are in the launch too,
+// as code of their own: as conditions inside the pass they cost every step 4 %.
+// Clamp and isolated modes, whose tiles do not depend on each other.
+// us of a 32-step call, a launch a step (replayed from graphs) / the middle
+// steps in one launch / all in one: 10 k hh 173 / 98 / 91, 67 k hh+pas in FP32
+// 201 / 90 / 84, 67 k of C5's mix in FP32 227 / 126 / 126, 15 k of eight types
+// 374 / 268 / 250, 266 k synapses 275 / 159 / 155; of a ten-step call on 1 k
+// instances of the mix 165 / 46 / 38.
 template <class S, int VM, bool EXT>
-__global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
+__global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps, int first_pass, int last_pass) {
     extern __shared__ double lds[];
     constexpr int PH = kDoCur | kDoState;
     constexpr bool NT = false;
@@ -1771,7 +1777,7 @@ __global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
     int *spk = (int *)q;
     for (int j = threadIdx.x; j < nn; j += blockDim.x) {
         const int n = nlo + j;
-        vl[j] = a.nd.v[n];
+        vl[j] = VM == MECH_V_CLAMP && first_pass ? clamp_v(a.nd, n, (double)a.kbase * a.g.dt) : a.nd.v[n];
         fx_zero(ar, j);
         fx_zero(ad, j);
         if (syn) sc[j] = 1e2 / a.nd.area[n];
@@ -1792,7 +1798,8 @@ __global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
     __syncthreads();
     for (int sub = 0; sub < nsteps; ++sub) {
         const long long k = a.kbase + sub;
-        MECH_TILE_PASS();
+        if (first_pass && sub == 0) MECH_TILE_PASS(kDoCur, PH);
+        else MECH_TILE_PASS(PH, PH);
         __syncthreads();
         const bool last = sub + 1 == nsteps;
         for (int j = threadIdx.x; j < nn; j += blockDim.x) {
@@ -1830,6 +1837,10 @@ __global__ __launch_bounds__(1024) void k_steps(FusedArgs a, int nsteps) {
             }
         }
         __syncthreads();
+    }
+    if (last_pass) {
+        const long long k = 0;
+        MECH_TILE_PASS(kDoState, PH);
     }
     if (flag) atomicOr(a.err, 1);
 }
@@ -2502,17 +2513,22 @@ size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion) {
     return (size_t)tile_nodes * (8 * res_node_doubles(vmode, syn, ion) + 4);
 }
 template <class S, bool EXT>
-static hipError_t steps_t(int vmode, const FusedArgs &a, int nsteps, int block, size_t lds, hipStream_t s) {
-    if (vmode == MECH_V_CLAMP) k_steps<S, MECH_V_CLAMP, EXT><<<a.n_tiles, block, lds, s>>>(a, nsteps);
-    else k_steps<S, MECH_V_ISOLATED, EXT><<<a.n_tiles, block, lds, s>>>(a, nsteps);
+static hipError_t steps_t(int vmode, const FusedArgs &a, int n, int first, int last, int block, size_t lds,
+                          hipStream_t s) {
+    if (vmode == MECH_V_CLAMP) k_steps<S, MECH_V_CLAMP, EXT><<<a.n_tiles, block, lds, s>>>(a, n, first, last);
+    else k_steps<S, MECH_V_ISOLATED, EXT><<<a.n_tiles, block, lds, s>>>(a, n, first, last);
     return hipGetLastError();
 }
-hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int block, int tn, hipStream_t s) {
-    if (a.n_tiles == 0 || nsteps <= 0) return hipSuccess;
+hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int first, int last, int block, int tn,
+                        hipStream_t s) {
+    if (a.n_tiles == 0) return hipSuccess;
     const bool ext = a.g.shared_ca || a.has_ext;
     const size_t lds = steps_lds_bytes(tn, vmode, a.has_syn != 0, a.g.shared_ca != 0);
-    if (ext) return fp32 ? steps_t<float, true>(vmode, a, nsteps, block, lds, s) : steps_t<double, true>(vmode, a, nsteps, block, lds, s);
-    return fp32 ? steps_t<float, false>(vmode, a, nsteps, block, lds, s) : steps_t<double, false>(vmode, a, nsteps, block, lds, s);
+    if (ext)
+        return fp32 ? steps_t<float, true>(vmode, a, nsteps, first, last, block, lds, s)
+                    : steps_t<double, true>(vmode, a, nsteps, first, last, block, lds, s);
+    return fp32 ? steps_t<float, false>(vmode, a, nsteps, first, last, block, lds, s)
+                : steps_t<double, false>(vmode, a, nsteps, first, last, block, lds, s);
 }
 
 size_t fused_lds_bytes(int tile_nodes, bool ion) { return (ion ? 9 : 6) * 8 * (size_t)tile_nodes; }

@@ -615,24 +615,24 @@ bool several_steps(const mech_ctx *c, int vmode) {
 
 int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, bool use_graph) {
     const GlobDev g = make_glob(c, dt);
-    if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
-    int rc = launch_fused_phase(c, kDoCur, vmode, g, k0, 0, c->stream);
-    if (rc) return rc;
-    // middle passes: state(k-1) + events(k) + cur(k) for k = k0+1 .. k0+nsteps-1:
-    // several per launch, or replayed from graphs of kGraphSteps passes and one
-    // of the remainder
-    int64_t mids = nsteps - 1, k = k0 + 1;
     if (several_steps(c, vmode)) {
         const Launch &l = c->batched();
         const int tn = (int)std::max<int64_t>(l.max_nodes, 1);
-        for (; mids > 0;) {
-            const int n = (int)std::min<int64_t>(mids, kStepsMax);
-            HIPCHK(c, launch_steps(c->fp32, vmode, fused_args(c, l, g, k, 0), n, l.block, tn, c->stream));
-            mids -= n;
-            k += n;
+        for (int64_t done = 0; done < nsteps;) {
+            const int n = (int)std::min<int64_t>(nsteps - done, kStepsMax);
+            HIPCHK(c, launch_steps(c->fp32, vmode, fused_args(c, l, g, k0 + done, 0), n, done == 0, done + n == nsteps,
+                                   l.block, tn, c->stream));
+            done += n;
         }
+        return MECH_OK;
     }
-    if (mids > 0) HIPCHK(c, launch_set_k((long long *)(c->buf + c->L.off_kdev), k, c->stream));
+    if (vmode == MECH_V_CLAMP) HIPCHK(c, launch_vclamp(c->nd, (double)k0 * dt, c->stream));
+    int rc = launch_fused_phase(c, kDoCur, vmode, g, k0, 0, c->stream);
+    if (rc) return rc;
+    // middle passes: state(k-1) + events(k) + cur(k) for k = k0+1 .. k0+nsteps-1,
+    // replayed from graphs of kGraphSteps passes and one of the remainder
+    int64_t mids = nsteps - 1;
+    if (mids > 0) HIPCHK(c, launch_set_k((long long *)(c->buf + c->L.off_kdev), k0 + 1, c->stream));
     while (use_graph && mids > 0) {
         const int n = (int)std::min<int64_t>(mids, kGraphSteps);
         hipGraphExec_t exec;

@@ -35,7 +35,7 @@ def test_own_shape_gives_the_same_bits(make, n):
 
 @pytest.mark.parametrize("vmode", ["clamp", "isolated"])
 @pytest.mark.parametrize("shared_ca", [0, 1])
-@pytest.mark.parametrize("steps", [2, 3, 260])
+@pytest.mark.parametrize("steps", [1, 2, 3, 256, 257, 260])
 def test_several_steps_a_launch_give_the_same_bits(vmode, shared_ca, steps):
     """Every type, ragged tiles, from no middle step to more than one launch
     holds, against a launch per step (a shape set by the caller)."""
