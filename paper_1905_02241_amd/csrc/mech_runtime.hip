@@ -188,6 +188,7 @@ void compute_layout(int64_t n_nodes, std::vector<SlotHost> &slots, int prec, Lay
 struct Launch {
     int block = 256, budget = 2048, nodes = 1024, blocks_per_cu = 0, flags = MECH_LAUNCH_XCD_ORDER;
     int64_t n_tiles = 0, max_nodes = 0, max_instances = 0;
+    int max_waves = 0;                // of a tile's runs, 64 instances a wave
     size_t first = 0;                 // first row in the device's table region
     std::vector<int32_t> rows;        // host copy of the tile table
 };
@@ -353,6 +354,7 @@ void make_tiles(const mech_ctx *c, Launch &l) {
                                       : (int32_t)(std::lower_bound(h.ni.begin(), h.ni.end(), (int32_t)node) - h.ni.begin()));
     };
     push(0);
+    const size_t row = 1 + c->slots.size();
     int64_t cost = 0, nodes = 0, max_nodes = 0, max_cost = 0;
     for (int64_t n = 0; n < c->n_nodes; ++n) {
         const int64_t cn = c->per_node[n];
@@ -369,9 +371,14 @@ void make_tiles(const mech_ctx *c, Launch &l) {
     max_nodes = std::max(max_nodes, nodes);
     max_cost = std::max(max_cost, cost);
     push(c->n_nodes);
-    l.n_tiles = c->n_nodes > 0 ? (int64_t)rows.size() / (1 + (int64_t)c->slots.size()) - 1 : 0;
+    l.n_tiles = c->n_nodes > 0 ? (int64_t)(rows.size() / row) - 1 : 0;
     l.max_nodes = max_nodes;
     l.max_instances = max_cost;
+    for (size_t t = 0; t < (size_t)l.n_tiles; ++t) {
+        int waves = 0;
+        for (size_t s = 1; s < row; ++s) waves += (rows[(t + 1) * row + s] - rows[t * row + s] + 63) / 64;
+        l.max_waves = std::max(l.max_waves, waves);
+    }
 }
 
 // Uploads the shape's tile table behind the first `first` rows.
@@ -402,6 +409,13 @@ int upload_tiles(mech_ctx *c, Launch &l, size_t first) {
 //     7813 (synapses)   1024 29.3, 2048 28.3
 //     32553 (C5's mix)  2048 and 448 nodes 130.2, 640 nodes 140.1; FP32 88.2, 96.1
 //     7813 (hh+pas)     448 nodes 29.1, 640 32.7; FP32 22.2, 25.3
+// Tiles of 256 instances of several types have more runs than four waves, and
+// a CU has one or two of them: a wave for each run of the largest tile, up to
+// eight.  us of a call with four waves / by this rule / with up to sixteen: 67 k
+// of C5's mix in FP32 128 / 122 / 122, 28 k of five types 151 / 140 / 140, 15 k
+// of eight types 477 / 477 / 484, six coupled cells 760 / 742 / 740.  Not for
+// tiles of 512: there the waves cost a CU workgroups (333 k of C5's mix 235 /
+// 294, 20 coupled cells 1362 / 1470).
 Launch fit_launch(const mech_ctx *c) {
     Launch l;
     int64_t total = 0;
@@ -931,6 +945,7 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
         // tiles of 64 instances); only a context of a few nodes has no room
         c->fit = fit_launch(c);
         make_tiles(c, c->fit);
+        if (c->fit.budget == 256) c->fit.block = std::clamp(64 * c->fit.max_waves, 256, 512);
         const size_t row = 1 + c->slots.size(), first = c->set.rows.size() / row;
         if (first + c->fit.rows.size() / row <= (size_t)c->L.max_tile_rows) rc = upload_tiles(c, c->fit, first);
         else c->fit = c->set;
