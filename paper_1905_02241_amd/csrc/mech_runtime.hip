@@ -212,10 +212,13 @@ struct mech_ctx {
     bool nodes_bound = false, clamp_bound = false, has_syn = false, cable_bound = false;
     // Launch shape and tile table of the time-fused path, and of the batched
     // path once the caller has chosen a shape; until then the batched path
-    // takes `fit`, the shape for the context's size.
+    // takes `fit`, the shape for the context's size, as the single phases
+    // always do.  `fit` is the caller's shape where the table region has no
+    // room for both tables (`placed`).
     Launch set, fit;
-    bool chosen = false;
-    const Launch &batched() const { return chosen ? set : fit; }
+    bool chosen = false, placed = false;
+    const Launch &own() const { return placed ? fit : set; }
+    const Launch &batched() const { return chosen ? set : own(); }
     int n_cu = 256;
     // time-fused path: steps per launch, and the dynamic LDS its kernels may take
     int res_steps = 64;
@@ -426,6 +429,16 @@ Launch fit_launch(const mech_ctx *c) {
     return l;
 }
 
+// Keeps the own shape's tile table behind the caller's.  The table region is
+// sized for tiles of 64 instances: it has room for both but in a context of a
+// few nodes or behind the smallest of tiles.
+int place_fit(mech_ctx *c) {
+    const size_t row = 1 + c->slots.size(), first = c->set.rows.size() / row;
+    if (c->placed && first <= c->fit.first) return MECH_OK;
+    c->placed = first + c->fit.rows.size() / row <= (size_t)c->L.max_tile_rows;
+    return c->placed ? upload_tiles(c, c->fit, first) : MECH_OK;
+}
+
 // Reject a step with unbound inputs before anything is enqueued.
 int check_ready(mech_ctx *c, int vmode) {
     if (!c->nodes_bound) return fail(c, MECH_ERR_STATE, "node vectors not bound (mech_bind_nodes)");
@@ -534,7 +547,7 @@ FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, 
 // asks for that path's scatter).
 constexpr size_t kPhaseLds = 65536;
 int launch_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int accumulate) {
-    const Launch &l = c->fit;
+    const Launch &l = c->own();
     const FusedArgs a = fused_args(c, l, g, k, 0);
     if (!cur) {
         HIPCHK(c, launch_phase_state(c->fp32, a, c->stream));
@@ -941,14 +954,10 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
         rc = upload_tiles(c, c->set, 0);
     }
     if (rc == MECH_OK) {
-        // the table region holds the tables of both shapes (it is sized for
-        // tiles of 64 instances); only a context of a few nodes has no room
         c->fit = fit_launch(c);
         make_tiles(c, c->fit);
         if (c->fit.budget == 256) c->fit.block = std::clamp(64 * c->fit.max_waves, 256, 512);
-        const size_t row = 1 + c->slots.size(), first = c->set.rows.size() / row;
-        if (first + c->fit.rows.size() / row <= (size_t)c->L.max_tile_rows) rc = upload_tiles(c, c->fit, first);
-        else c->fit = c->set;
+        rc = place_fit(c);
     }
     if (rc != MECH_OK) {
         g_last_error = c->err;
@@ -1369,7 +1378,8 @@ int mech_set_launch(mech_ctx *c, int block, int tile_instances, int tile_nodes, 
     c->set.flags = flags;
     c->chosen = true;
     make_tiles(c, c->set);
-    return upload_tiles(c, c->set, 0);
+    const int rc = upload_tiles(c, c->set, 0);
+    return rc ? rc : place_fit(c);   // its table moves with the end of the caller's
 }
 
 int mech_get_launch(const mech_ctx *c, int *block, int *tile_instances, int *tile_nodes, int *blocks_per_cu,

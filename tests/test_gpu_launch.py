@@ -110,6 +110,24 @@ def test_single_phases_match_the_oracle(name, shared_ca):
             assert np.array_equal(b[key], 2.0 * a[key]), key
 
 
+@pytest.mark.parametrize("shape", [(64, 64, 64, 0, 1), (256, 256, 128, 0, 1), (256, 4096, 2048, 0, 1)])
+def test_single_phases_after_a_chosen_shape(shape):
+    """The caller's tile table may be longer than the one it replaces: the
+    single phases, which keep their own, give the bits they gave before."""
+    from paper_1905_02241_amd import mech
+    w = W.make_tiny(88, kinds=W.KINDS, n_nodes=3001, vmode="external", syn_per_node=2.0)
+
+    def phases(shapes):
+        m = mech.from_workload(w, "fp64")
+        for k, s in enumerate(shapes):
+            if s:
+                m.set_launch(*s)
+            m.cur(k, w.dt)
+            m.state(w.dt)
+        return {**m.nodes(), "states": mech.states_of(m)}
+    same(phases([None] * 4), phases([None, shape, (128, 256, 64, 0, 1), shape]))
+
+
 def test_resident_tile_without_room_for_the_table_of_runs():
     """A tile that fills the LDS of a workgroup to within the 2 KiB that the
     table would take: its waves find their runs by the ends."""
