@@ -189,6 +189,8 @@ struct Launch {
     int block = 256, budget = 2048, nodes = 1024, blocks_per_cu = 0, flags = MECH_LAUNCH_XCD_ORDER;
     int64_t n_tiles = 0, max_nodes = 0, max_instances = 0;
     int max_waves = 0;                // of a tile's runs, 64 instances a wave
+    int waves = 0;                    // that the batched path launches a tile with; 0: block's
+    int threads() const { return waves ? 64 * waves : block; }
     size_t first = 0;                 // first row in the device's table region
     std::vector<int32_t> rows;        // host copy of the tile table
 };
@@ -419,13 +421,14 @@ int upload_tiles(mech_ctx *c, Launch &l, size_t first) {
 // of eight types 477 / 477 / 484, six coupled cells 760 / 742 / 740.  Not for
 // tiles of 512: there the waves cost a CU workgroups (333 k of C5's mix 235 /
 // 294, 20 coupled cells 1362 / 1470).
+constexpr int kFitNodes = 448;
 Launch fit_launch(const mech_ctx *c) {
     Launch l;
     int64_t total = 0;
     for (const auto &h : c->slots) total += h.n;
     const int64_t w = total / c->n_cu;
     l.budget = w < 512 ? 256 : w < 2048 ? 512 : w < 7000 ? 1024 : 2048;
-    l.nodes = std::min(l.budget, 448);
+    l.nodes = std::min(l.budget, kFitNodes);
     return l;
 }
 
@@ -575,7 +578,7 @@ int launch_fused_phase(mech_ctx *c, int phases, int vmode, const GlobDev &g, int
     const int vm = vmode == MECH_V_CABLE ? MECH_V_EXTERNAL : vmode;
     const Launch &l = c->batched();
     const int tn = (int)std::max<int64_t>(l.max_nodes, 1);
-    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, l, g, k, kofs), fused_grid(c, l), l.block, tn, s));
+    HIPCHK(c, launch_fused(c->fp32, phases, vm, fused_args(c, l, g, k, kofs), fused_grid(c, l), l.threads(), tn, s));
     if (vmode == MECH_V_CABLE && (phases & kDoCur)) HIPCHK(c, launch_cable(c->cable, c->nd, g, s));
     return MECH_OK;
 }
@@ -648,7 +651,7 @@ int step_batched(mech_ctx *c, int64_t nsteps, int64_t k0, double dt, int vmode, 
         for (int64_t done = 0; done < nsteps;) {
             const int n = (int)std::min<int64_t>(nsteps - done, kStepsMax);
             HIPCHK(c, launch_steps(c->fp32, vmode, fused_args(c, l, g, k0 + done, 0), n, done == 0, done + n == nsteps,
-                                   l.block, tn, c->stream));
+                                   l.threads(), tn, c->stream));
             done += n;
         }
         return MECH_OK;
@@ -956,7 +959,7 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
     if (rc == MECH_OK) {
         c->fit = fit_launch(c);
         make_tiles(c, c->fit);
-        if (c->fit.budget == 256) c->fit.block = std::clamp(64 * c->fit.max_waves, 256, 512);
+        if (c->fit.budget == 256) c->fit.waves = std::clamp(c->fit.max_waves, 4, 8);
         rc = place_fit(c);
     }
     if (rc != MECH_OK) {
@@ -1376,7 +1379,9 @@ int mech_set_launch(mech_ctx *c, int block, int tile_instances, int tile_nodes, 
     c->set.nodes = tile_nodes;
     c->set.blocks_per_cu = blocks_per_cu;
     c->set.flags = flags;
-    c->chosen = true;
+    // the own shape by another name is the own shape (and its launches)
+    c->chosen = block != c->fit.block || tile_instances != c->fit.budget || tile_nodes != c->fit.nodes ||
+                blocks_per_cu != c->fit.blocks_per_cu || flags != c->fit.flags;
     make_tiles(c, c->set);
     const int rc = upload_tiles(c, c->set, 0);
     return rc ? rc : place_fit(c);   // its table moves with the end of the caller's

@@ -48,6 +48,19 @@ def test_several_steps_a_launch_give_the_same_bits(vmode, shared_ca, steps):
         assert np.array_equal(ma.ion(name), mb.ion(name)), name
 
 
+@pytest.mark.parametrize("model", ["hh", "mixed"])
+def test_own_shape_by_name_is_the_own_shape(model):
+    """What mech_get_launch reports can be set and changes nothing: a small
+    context's steps stay together in one launch."""
+    from paper_1905_02241_amd import mech
+    w = W.make_c1(n_nodes=3000) if model == "hh" else W.make_c5(n_nodes=3000)
+    shape = mech.from_workload(w, "fp64").get_launch()
+    a, _ = run_gpu(w, 9, "batched", "fp64")
+    b, mb = run_gpu(w, 9, "batched", "fp64", launch=shape)
+    same(a, b)
+    assert tuple(mb.get_launch()) == tuple(shape)
+
+
 def crowded():
     """One node with more instances than a tile's LDS holds, its neighbours
     with none or a few."""
