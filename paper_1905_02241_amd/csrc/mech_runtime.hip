@@ -1447,14 +1447,19 @@ static int autotune_impl(mech_ctx *c, double dt, int vmode, int nsteps, int reps
     struct Shape { int block, budget, nodes, bpc, flags; };
     std::vector<Shape> cand;
     if (!resident) {
-        // the non-temporal flag measured slower on every shape tried; it
-        // stays available through mech_set_launch but is not searched
+        // the own shape first: it alone takes several steps a launch where
+        // that pays.  The non-temporal flag measured slower on every shape
+        // tried; it stays available through mech_set_launch but is not
+        // searched.
+        cand.push_back({c->fit.block, c->fit.budget, c->fit.nodes, c->fit.blocks_per_cu, c->fit.flags});
         for (int b : {128, 256, 512})
             for (int ipt : {1, 2, 4, 8})
                 for (int bpc : {0, 1, 2, 8})
                     for (int fl : {0, (int)MECH_LAUNCH_XCD_ORDER}) {
                         const int budget = b * ipt;
                         cand.push_back({b, budget, std::min(kMaxTileNodes, std::max(kMinTileNodes, budget)), bpc, fl});
+                        // the node span that lets seven workgroups share a CU's LDS
+                        if (bpc == 0 && budget > kFitNodes) cand.push_back({b, budget, kFitNodes, bpc, fl});
                     }
     } else {
         // a tile stays on one CU for many steps, so its LDS (and how many
