@@ -19,6 +19,7 @@ constexpr int kMinTileBudget = 64;   // smallest tile work budget (instances)
 constexpr int kMinTileNodes = 64;
 constexpr int kMaxPerNode = 1 << 19; // instances on one node: the fused paths' fixed-point node sums stay exact
 constexpr int kMaxTileNodes = 2048;  // LDS: 48 B per node -> 96 KiB per block (144 KiB with the shared calcium ion)
+constexpr int kLongRun = 80;         // instances of a type on a node that a wave of k_phase_cur sums, not a thread
 
 // Step-phase flags of the fused kernel.
 enum : int { kDoState = 1, kDoCur = 2 };
@@ -216,10 +217,10 @@ hipError_t launch_cable_coeffs(const CableDev &c, const double *area, hipStream_
 hipError_t launch_fused(bool fp32, int phases, int vmode, const FusedArgs &a, int grid, int block, int tile_nodes,
                         hipStream_t s);
 size_t fused_lds_bytes(int tile_nodes, bool ion);
-hipError_t launch_phase_cur(bool fp32, const FusedArgs &a, int accumulate, int tile_nodes, int tile_instances,
-                            hipStream_t s);
+hipError_t launch_phase_cur(bool fp32, const FusedArgs &a, int accumulate, bool crowded, int tile_nodes,
+                            int tile_instances, hipStream_t s);
 hipError_t launch_phase_state(bool fp32, const FusedArgs &a, hipStream_t s);
-size_t phase_lds_bytes(int tile_nodes, int tile_instances, int n_slots, bool ion);
+size_t phase_lds_bytes(int tile_nodes, int tile_instances, int n_slots, bool ion, bool crowded);
 hipError_t launch_steps(bool fp32, int vmode, const FusedArgs &a, int nsteps, int first, int last, int block,
                         int tile_nodes, hipStream_t s);
 size_t steps_lds_bytes(int tile_nodes, int vmode, bool syn, bool ion);

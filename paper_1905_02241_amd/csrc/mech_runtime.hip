@@ -82,6 +82,7 @@ struct SlotHost {
     bool identity = false;
     bool perm_identity = true;
     bool crossing = false;         // a node's run crosses a multiple of 64 instances (kPad, a wave)
+    bool crowded = false;          // a node has kLongRun instances or more
     std::vector<int32_t> perm;     // internal -> caller index (empty when identity)
     std::vector<int32_t> ni;       // node index, internal (sorted) order
     size_t off_ni = 0, off_gid = 0, off_ica = 0;
@@ -559,10 +560,12 @@ int launch_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int accumul
         return MECH_OK;
     }
     const int tn = (int)std::max<int64_t>(l.max_nodes, 1), ti = (int)((l.max_instances + 3) & ~(int64_t)3);
+    bool crowded = false;
+    for (const SlotHost &h : c->slots) crowded |= h.crowded;
     if ((c->set.flags & MECH_LAUNCH_PLAIN_ATOMIC) || ti >= 0xffff ||
-        phase_lds_bytes(tn, ti, a.n_slots, g.shared_ca != 0) > kPhaseLds)
+        phase_lds_bytes(tn, ti, a.n_slots, g.shared_ca != 0, crowded) > kPhaseLds)
         return launch_plain_phase(c, true, k, g, accumulate);
-    HIPCHK(c, launch_phase_cur(c->fp32, a, accumulate, tn, ti, c->stream));
+    HIPCHK(c, launch_phase_cur(c->fp32, a, accumulate, crowded, tn, ti, c->stream));
     return MECH_OK;
 }
 
@@ -886,8 +889,10 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
             }
         }
     }
-    for (SlotHost &h : c->slots)
+    for (SlotHost &h : c->slots) {
         for (int64_t i = kPad; i < h.n && !h.crossing; i += kPad) h.crossing = h.ni[i] == h.ni[i - 1];
+        for (int64_t i = kLongRun - 1; i < h.n && !h.crowded; ++i) h.crowded = h.ni[i] == h.ni[i - (kLongRun - 1)];
+    }
     {
         // the fused paths sum a node's contributions in fixed point, exact up
         // to kMaxPerNode of them
