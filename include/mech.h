@@ -326,7 +326,8 @@ int mech_set_resident_steps(mech_ctx *ctx, int steps_per_launch);
  * 10/16 to 20/16 of the fastest one's, keep the fastest, and return its ms
  * per step.  STATEs, v, rhs, d, spike counts and the per-node calcium ion are
  * saved before and restored after, so the call has no visible effect
- * besides the chosen shape.                                                */
+ * besides the chosen shape.  A search that fails or finds no shape leaves
+ * the shapes of both paths as they were.                                   */
 int mech_autotune(mech_ctx *ctx, double dt, int vmode, int nsteps, int reps, double *best_ms_per_step);
 
 /* The same for the RESIDENT path (with the same second round and tile

@@ -1443,8 +1443,9 @@ static int autotune_impl(mech_ctx *c, double dt, int vmode, int nsteps, int reps
     };
     hipError_t e = copy_all(true);
     if (e != hipSuccess) { (void)hipFree(save); return fail(c, MECH_ERR_HIP, "autotune save: %s", hipGetErrorString(e)); }
-    const Launch &now = resident ? c->set : c->batched();
-    int best[5] = {now.block, now.budget, now.nodes, now.blocks_per_cu, now.flags};
+    const Launch before = c->set;
+    const bool chosen = c->chosen;
+    int best[5] = {};
     double best_t = 1e300;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     (void)hipEventCreate(&e0);
@@ -1552,7 +1553,16 @@ static int autotune_impl(mech_ctx *c, double dt, int vmode, int nsteps, int reps
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    int rc2 = mech_set_launch(c, best[0], best[1], best[2], best[3], best[4]);
+    int rc2;
+    if (rc == MECH_OK && best_t < 1e299) {
+        rc2 = mech_set_launch(c, best[0], best[1], best[2], best[3], best[4]);
+    } else {
+        // no shape found: both paths keep the one they had
+        c->set = before;
+        c->chosen = chosen;
+        rc2 = upload_tiles(c, c->set, 0);
+        if (rc2 == MECH_OK) rc2 = place_fit(c);
+    }
     e = copy_all(false);
     (void)hipFree(save);
     if (rc) return rc;
