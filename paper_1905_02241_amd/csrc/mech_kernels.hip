@@ -1426,13 +1426,8 @@ __device__ __forceinline__ void fx_add(Acc a, int j, double x, int &flag) {
     atomicAdd(a.hi + j, (unsigned long long)h);
     atomicAdd(a.lo + j, (unsigned long long)l);
 }
-// The total (H 2^44 + L) 2^-67 of the two words' signed sums: both convert to
-// FP64 exactly below 2^53 (H: a node's |x| adding up to less than 2^30; L: at
-// most 2^10 contributions; beyond that each within one rounding of itself),
-// and the fused multiply-add rounds their sum once.
-__device__ __forceinline__ double fx_get(Acc a, int j) {
-    return fma((double)(long long)a.lo[j], 0x1p-67, (double)(long long)a.hi[j] * 0x1p-23);
-}
+// The total of the two words, rounded once.
+__device__ __forceinline__ double fx_get(Acc a, int j) { return fx_total((long long)a.hi[j], (long long)a.lo[j]); }
 
 // LDS per tile node: v and 100/area (two doubles), the rhs and d
 // accumulators (four 64-bit words); under the shared calcium ion also the

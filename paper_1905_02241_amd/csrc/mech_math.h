@@ -165,4 +165,19 @@ MECH_HD_INLINE double sin_d(double x) {
     return (q >= 2.0) ? -y : y;
 }
 
+// The total (H 2^44 + L) 2^-67 of a fixed-point node sum's two signed words
+// (mech_kernels.hip).  L's upper 20 bits are carried to H's place, so that every
+// part is exact in FP64 while |total| < 2^30 and the last fused multiply-add
+// rounds their sum once, whatever the number of contributions; beyond that H's
+// part is rounded as well, and the result is within 1.5 ulp.  (Converted as one
+// number L exceeds 2^53 from 2^10 contributions on, and where it cancels against
+// H its rounding is what is left: over 1e-12 of some sums in tests/fixed_point.cpp.)
+// L's low 44 bits convert by their place in the mantissa of 2^52.
+MECH_HD_INLINE double fx_total(long long H, long long L) {
+    const long long low = (L & 0xfffffffffffll) | 0x4330000000000000ll;
+    const double h0 = (double)(unsigned)H + (double)((int)(L >> 32) >> 12);
+    const double h = fma((double)(int)(H >> 32), 0x1p9, h0 * 0x1p-23);
+    return fma(__builtin_bit_cast(double, low) - 0x1p52, 0x1p-67, h);
+}
+
 }  // namespace mech
