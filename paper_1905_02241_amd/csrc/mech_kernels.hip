@@ -894,9 +894,6 @@ __device__ __forceinline__ TreeRecs tree_recs(const TreeUnit &u, const char *at,
     const char *b = at - from;
     return TreeRecs{b, b + u.o_more, b + u.o_fold, b + u.o_elim, (const int *)(b + u.o_rf), (const int *)(b + u.o_re), u.nr};
 }
-// Bytes of a unit's rows in LDS: its own and the one that stands for a missing
-// neighbour.
-__device__ __forceinline__ int tree_bytes(int np) { return 32 * (np + 1); }
 __device__ __forceinline__ double *tree_rows(char *lds, int np) {
     double *rows = (double *)lds;
     if (threadIdx.x == 0) {
@@ -1217,9 +1214,8 @@ __global__ __launch_bounds__(1024) void k_tree_a(CableDev c, NodesDev nd, GlobDe
     const TreeUnit u = c.units_a[blockIdx.x];
     const int tid = (int)threadIdx.x, B = (int)blockDim.x, p0 = u.p0, np = u.np;
     double *r = tree_rows(tree_lds, np);
-    char *tab = tree_lds + tree_bytes(np);
-    tree_copy(tab, c.block + 16 * (size_t)u.block,
-              u.mode == kUnitFull ? u.bytes : u.mode == kUnitPiece ? u.o_re : u.o_fold);
+    char *tab = tree_lds + tree_row_bytes(np);
+    tree_copy(tab, c.block + 16 * (size_t)u.block, tree_up_bytes(u.mode, u.bytes, u.o_re, u.o_fold));
     const TreeRecs rc = tree_recs(u, tab, 0);
     TreeKeep keep;
     tree_assemble<true, false>(c, nd, g, r, rc, p0, np, keep);
@@ -1255,7 +1251,7 @@ __global__ __launch_bounds__(1024) void k_tree_top(CableDev c, NodesDev nd, Glob
     TreeRecs rc;
     if constexpr (LDS) {
         r = tree_rows(tree_lds, u.np);
-        char *tab = tree_lds + tree_bytes(u.np);
+        char *tab = tree_lds + tree_row_bytes(u.np);
         tree_copy(tab, block, u.bytes);
         rc = tree_recs(u, tab, 0);
     } else {
@@ -1295,7 +1291,7 @@ __global__ __launch_bounds__(1024) void k_tree_b(CableDev c, NodesDev nd, GlobDe
     TreeRecs rp{};
     if (piece) {
         tree_copy(at, c.G + 4 * (size_t)p0, 32 * np);
-        at += tree_bytes(np);
+        at += tree_row_bytes(np);
         tree_copy(at, c.block + 16 * (size_t)u.block + u.o_re, u.bytes - u.o_re);
         rp = tree_recs(u, at, u.o_re);
         at += u.bytes - u.o_re;
@@ -1304,7 +1300,7 @@ __global__ __launch_bounds__(1024) void k_tree_b(CableDev c, NodesDev nd, GlobDe
     if (trunk) {
         const int nt = t.np;
         r = tree_rows(at, nt);
-        char *tab = at + tree_bytes(nt);
+        char *tab = at + tree_row_bytes(nt);
         tree_copy(tab, c.block + 16 * (size_t)t.block, t.bytes);
         const TreeRecs rc = tree_recs(t, tab, 0);
         for (int i = tid; i < nt; i += B) {

@@ -1113,77 +1113,11 @@ int mech_bind_cable(mech_ctx *c, const int32_t *parent, const double *g_axial, i
         build_schedule(h, s);
         tree_tables(h, s, t);
     }
-    // Trunks that every piece of the cell has room for beside its own rows
-    // are solved by the pieces; the others take a launch of their own.
-    const int U = (int)t.unit.size();
-    auto row_bytes = [](const TreeUnit &u) { return 32 * ((size_t)u.np + 1); };
-    auto trunk_bytes = [&](const TreeUnit &u) { return row_bytes(u) + (size_t)u.bytes; };
-    auto piece_bytes = [&](const TreeUnit &u) { return row_bytes(u) + (size_t)(u.bytes - u.o_re); };
-    std::vector<int> trunk_of;
-    std::vector<size_t> piece_max;
-    for (int u = 0; u < U; ++u) {
-        if (t.unit[u].nr > (t.unit[u].wide ? kTreeRounds : 63))
-            return fail(c, MECH_ERR_STATE, "internal: %d elimination rounds in a unit", t.unit[u].nr);
-        if (h.cell_of[u] < 0) continue;
-        const size_t cell = (size_t)h.cell_of[u];
-        if (trunk_of.size() <= cell) {
-            trunk_of.resize(cell + 1, -1);
-            piece_max.resize(cell + 1, 0);
-        }
-        if (t.unit[u].mode == kUnitTop) trunk_of[cell] = u;
-        else piece_max[cell] = std::max(piece_max[cell], piece_bytes(t.unit[u]));
-    }
-    std::vector<char> shared(U, 0);
-    std::vector<TreeUnit> ua, ut, ug, ub;
-    size_t lds_a = 0, lds_top = 0, lds_b = 0, rows_a = 0, rows_b = 0;
-    for (int32_t u : h.list_top)
-        shared[u] = trunk_bytes(t.unit[u]) + piece_max[h.cell_of[u]] <= (size_t)lds_bytes;
-    for (int32_t u : h.list_up) {
-        TreeUnit &x = t.unit[u];
-        if (x.mode == kUnitPiece) x.solves_trunk = shared[trunk_of[h.cell_of[u]]];
-        ua.push_back(x);
-        lds_a = std::max(lds_a, row_bytes(x) + (size_t)(x.mode == kUnitFull ? x.bytes : x.o_re));
-        rows_a = std::max(rows_a, (size_t)x.np);
-    }
-    for (int32_t u : h.list_down) {
-        const TreeUnit &x = t.unit[u];
-        if (x.mode != kUnitPiece) continue;
-        const TreeUnit &y = t.unit[trunk_of[h.cell_of[u]]];
-        ub.push_back(x);
-        ub.push_back(y);
-        lds_b = std::max(lds_b, piece_bytes(x) + (x.solves_trunk ? trunk_bytes(y) : 0));
-        rows_b = std::max(rows_b, (size_t)x.np);
-    }
-    for (int32_t u : h.list_top) {
-        const TreeUnit &x = t.unit[u];
-        rows_a = std::max(rows_a, (size_t)x.np);
-        if (shared[u]) {
-            ua.push_back(x);
-            lds_a = std::max(lds_a, row_bytes(x) + (size_t)x.o_fold);
-            ub.push_back(x);
-            ub.push_back(x);
-            lds_b = std::max(lds_b, trunk_bytes(x));
-            rows_b = std::max(rows_b, (size_t)x.np);
-        } else {
-            ut.push_back(x);
-            lds_top = std::max(lds_top, trunk_bytes(x));
-        }
-    }
-    for (int32_t u : h.list_top_g) ug.push_back(t.unit[u]);
-    std::vector<int32_t> pos(4 * h.pos_node.size());
-    for (int u = 0; u < U; ++u)
-        for (int p = h.unit_pos[u]; p < h.unit_pos[u + 1]; ++p) {
-            pos[4 * (size_t)p] = h.pos_node[p];
-            pos[4 * (size_t)p + 1] = h.pos_pnode[p];
-            pos[4 * (size_t)p + 2] = -1;
-            pos[4 * (size_t)p + 3] = h.pos_par[p] >= 0 ? -1 : -2;
-        }
-    for (int u = 0; u < U; ++u)
-        for (int p = h.unit_pos[u]; p < h.unit_pos[u + 1]; ++p)
-            if (const int src = h.pos_src[p]; src >= 0) {
-                pos[4 * (size_t)p + 2] = src;
-                if (shared[u]) pos[4 * (size_t)src + 3] = p - h.unit_pos[u];
-            }
+    for (const TreeUnit &u : t.unit)
+        if (u.nr > (u.wide ? kTreeRounds : 63))
+            return fail(c, MECH_ERR_STATE, "internal: %d elimination rounds in a unit", u.nr);
+    TreeLaunches l;
+    tree_launches(h, t, (size_t)lds_bytes, l);
     // one upload of everything but the double arrays
     std::vector<char> img(offs[kCabUploaded]);
     bool fits = true;
@@ -1192,12 +1126,12 @@ int mech_bind_cable(mech_ctx *c, const int32_t *parent, const double *g_axial, i
         else if (bytes) memcpy(img.data() + offs[j], p, bytes);
     };
     put(kCabParent, h.parent.data(), 4 * h.parent.size());
-    put(kCabPos, pos.data(), 4 * pos.size());
+    put(kCabPos, l.pos.data(), 4 * l.pos.size());
     put(kCabUnits, t.unit.data(), sizeof(TreeUnit) * t.unit.size());
-    put(kCabUnitsA, ua.data(), sizeof(TreeUnit) * ua.size());
-    put(kCabUnitsTop, ut.data(), sizeof(TreeUnit) * ut.size());
-    put(kCabUnitsTopG, ug.data(), sizeof(TreeUnit) * ug.size());
-    put(kCabUnitsB, ub.data(), sizeof(TreeUnit) * ub.size());
+    put(kCabUnitsA, l.a.data(), sizeof(TreeUnit) * l.a.size());
+    put(kCabUnitsTop, l.top.data(), sizeof(TreeUnit) * l.top.size());
+    put(kCabUnitsTopG, l.top_g.data(), sizeof(TreeUnit) * l.top_g.size());
+    put(kCabUnitsB, l.b.data(), sizeof(TreeUnit) * l.b.size());
     put(kCabBlock, t.block.data(), t.block.size());
     if (!fits) return fail(c, MECH_ERR_STATE, "internal: a cable array exceeds its bound");
     char *b = (char *)dev_buf;
@@ -1214,18 +1148,18 @@ int mech_bind_cable(mech_ctx *c, const int32_t *parent, const double *g_axial, i
     d.units_top_g = units(kCabUnitsTopG);
     d.units_b = units(kCabUnitsB);
     d.block = b + offs[kCabBlock];
-    d.n_units = U;
-    d.n_a = (int)ua.size();
-    d.n_top = (int)ut.size();
-    d.n_top_g = (int)ug.size();
-    d.n_b = (int)ub.size() / 2;
-    d.lds_a = (int)lds_a;
-    d.lds_top = (int)lds_top;
-    d.lds_b = (int)lds_b;
+    d.n_units = (int)t.unit.size();
+    d.n_a = (int)l.a.size();
+    d.n_top = (int)l.top.size();
+    d.n_top_g = (int)l.top_g.size();
+    d.n_b = (int)l.b.size() / 2;
+    d.lds_a = (int)l.lds_a;
+    d.lds_top = (int)l.lds_top;
+    d.lds_b = (int)l.lds_b;
     // a thread for every two rows of the largest unit
     auto block = [](size_t rows) { return (int)std::min<size_t>(1024, std::max<size_t>(64, (rows / 2 + 63) / 64 * 64)); };
-    d.block_a = block(rows_a);
-    d.block_b = block(rows_b);
+    d.block_a = block(l.rows_a);
+    d.block_b = block(l.rows_b);
     d.pa = D(kCabPa);
     d.pu = D(kCabPu);
     d.G = D(kCabG);

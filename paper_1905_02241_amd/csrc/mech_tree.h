@@ -481,4 +481,91 @@ inline void tree_tables(const CableHost &h, const TreeSchedule &s, TreeTables &d
     }
 }
 
+// LDS bytes of a unit's rows (S, T, U, N each): its own and the one that stands
+// for a missing neighbour.
+constexpr int tree_row_bytes(int np) { return 32 * (np + 1); }
+// Bytes of a unit's block that the first launch copies to LDS: whole cells need
+// all of it, pieces what leads to their roots, trunks the children alone (the
+// last launch takes a piece's block from o_re on).  By value: a reference to the
+// unit kept it in memory on the device, 68 bytes of scratch a lane and 12 % of a
+// solve.
+constexpr int tree_up_bytes(int mode, int bytes, int o_re, int o_fold) {
+    return mode == kUnitFull ? bytes : mode == kUnitPiece ? o_re : o_fold;
+}
+
+// What the launches of a solve run, a unit (in `b` a pair) a workgroup, and their
+// sizes.  Trunks that every piece of the cell has room for beside its own rows
+// are solved by the pieces; the others take a launch of their own.
+struct TreeLaunches {
+    std::vector<int32_t> pos;   // four per position (CableDev::pos)
+    std::vector<TreeUnit> a, top, top_g, b;
+    size_t lds_a = 0, lds_top = 0, lds_b = 0;   // dynamic LDS
+    size_t rows_a = 0, rows_b = 0;              // rows of the largest unit
+};
+inline void tree_launches(const CableHost &h, TreeTables &t, size_t lds_bytes, TreeLaunches &l) {
+    l = TreeLaunches();
+    const int U = (int)t.unit.size();
+    auto alone = [](const TreeUnit &u) { return (size_t)tree_row_bytes(u.np) + u.bytes; };
+    auto down = [](const TreeUnit &u) { return (size_t)tree_row_bytes(u.np) + u.bytes - u.o_re; };
+    auto grow = [](size_t &x, size_t y) { x = std::max(x, y); };
+    std::vector<int> trunk_of;
+    std::vector<size_t> piece_max;
+    for (int u = 0; u < U; ++u) {
+        if (h.cell_of[u] < 0) continue;
+        const size_t cell = (size_t)h.cell_of[u];
+        if (trunk_of.size() <= cell) {
+            trunk_of.resize(cell + 1, -1);
+            piece_max.resize(cell + 1, 0);
+        }
+        if (t.unit[u].mode == kUnitTop) trunk_of[cell] = u;
+        else grow(piece_max[cell], down(t.unit[u]));
+    }
+    std::vector<char> shared(U, 0);
+    for (int32_t u : h.list_top) shared[u] = alone(t.unit[u]) + piece_max[h.cell_of[u]] <= lds_bytes;
+    auto first = [&](const TreeUnit &x) {
+        l.a.push_back(x);
+        grow(l.lds_a, (size_t)tree_row_bytes(x.np) + tree_up_bytes(x.mode, x.bytes, x.o_re, x.o_fold));
+        grow(l.rows_a, (size_t)x.np);
+    };
+    auto last = [&](const TreeUnit &x, const TreeUnit &trunk, size_t bytes) {
+        l.b.push_back(x);
+        l.b.push_back(trunk);
+        grow(l.lds_b, bytes);
+        grow(l.rows_b, (size_t)x.np);
+    };
+    for (int32_t u : h.list_up) {
+        TreeUnit &x = t.unit[u];
+        if (x.mode == kUnitPiece) x.solves_trunk = shared[trunk_of[h.cell_of[u]]];
+        first(x);
+    }
+    for (int32_t u : h.list_down) {
+        const TreeUnit &x = t.unit[u];
+        if (x.mode != kUnitPiece) continue;
+        const TreeUnit &y = t.unit[trunk_of[h.cell_of[u]]];
+        last(x, y, down(x) + (x.solves_trunk ? alone(y) : 0));
+    }
+    for (int32_t u : h.list_top) {
+        const TreeUnit &x = t.unit[u];
+        if (shared[u]) {
+            first(x);
+            last(x, x, alone(x));
+        } else {
+            l.top.push_back(x);
+            grow(l.lds_top, alone(x));
+            grow(l.rows_a, (size_t)x.np);
+        }
+    }
+    for (int32_t u : h.list_top_g) l.top_g.push_back(t.unit[u]);
+    l.pos.resize(4 * h.pos_node.size());
+    for (size_t p = 0; p < h.pos_node.size(); ++p) {
+        l.pos[4 * p] = h.pos_node[p];
+        l.pos[4 * p + 1] = h.pos_pnode[p];
+        l.pos[4 * p + 2] = h.pos_src[p];
+        l.pos[4 * p + 3] = h.pos_par[p] >= 0 ? -1 : -2;
+    }
+    for (int u = 0; u < U; ++u)
+        for (int p = h.unit_pos[u]; p < h.unit_pos[u + 1]; ++p)
+            if (const int src = h.pos_src[p]; src >= 0 && shared[u]) l.pos[4 * (size_t)src + 3] = p - h.unit_pos[u];
+}
+
 }  // namespace mech
