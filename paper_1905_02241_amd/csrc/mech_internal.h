@@ -103,6 +103,7 @@ struct CableDev {
     // rounds as quotients (its roots' as they are, then with dv), the rows of
     // trunks that pieces solve, the rows of trunks in global memory
     double *G;
+    double *N;                 // per position of a trunk in global memory: N while its rows are there
 };
 
 struct FusedArgs {

@@ -31,6 +31,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace mech {
 
 // ------------------------------------------------------------ FP32 math --
@@ -800,15 +802,20 @@ __global__ void k_visolated(NodesDev nd, GlobDev g) {
 // the mechanisms' rhs and d.  Row n, scaled by a_n = area_n/100 so that both
 // ends of an edge see the same conductance g:
 //   S_n dv_n - sum_j g_nj dv_j = T_n,
-//   S_n = a_n (1e-3 cm/dt + d_n) + sum_j g_nj,
+//   S_n = L_n + sum_j g_nj, L_n = a_n (1e-3 cm/dt + d_n),
 //   T_n = a_n rhs_n + sum_j g_nj (v_j - v_n).
 // A round (mech_tree.h) eliminates rows i that have a parent p (coupling U_i)
 // and at most one child c (coupling N_i, until then U_c):
-//   S_p -= U_i^2/S_i, T_p += T_i U_i/S_i, and the same for c with N_i; c then
-//   hangs off p with U_c = N_i U_i/S_i.
-// After the last round dv = T/S at the roots, and the rounds are walked
-// backwards with dv_i = (T_i + U_i dv_p + N_i dv_c)/S_i, whose three quotients
-// are formed for all rows at once beforehand.
+//   S_p -= U_i^2/S_i, L_p += L_i U_i/S_i, T_p += T_i U_i/S_i, and the same for c
+//   with N_i; c then hangs off p with U_c = N_i U_i/S_i.
+// After the last round dv = T/L at the roots, and the rounds are walked
+// backwards with dv_i = (T_i + U_i dv_p + N_i dv_c)/(L_i + U_i + N_i), whose
+// three quotients are formed for all rows at once beforehand.
+// The differences S lose to cancellation what the couplings exceed L by; as
+// factors they hardly pass it on.  rms error of dv over steps 0 to 200 of eight
+// models against 128-bit arithmetic: 0.57 to 0.91 (once 1.2) of Hines
+// elimination's in FP64; walking back with S too it was 0.62 to 1.54, above 1.4
+// in every first step.
 //
 // A unit's rows and records sit in LDS.  What bounds the solve is the chain of
 // dependent rounds and the memory latencies before and after them, not bytes:
@@ -830,24 +837,26 @@ __global__ void k_visolated(NodesDev nd, GlobDev g) {
 // Solve of 64 cells of 200 to 20 000 compartments (369 k in all): 36 us a step,
 // where elimination by heights in three launches took 88; of 6 cells of 200 to
 // 2000 (5.8 k): 15 us, where it took 48.
-// A row: S, T, U and N side by side, 32 bytes.
+// A row: L, T, U and S side by side, 32 bytes; of an eliminated row with a child
+// left N in place of S.
 typedef double f64x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ f64x2 row_st(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i); }
-__device__ __forceinline__ f64x2 row_un(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i + 2); }
-__device__ __forceinline__ void set_st(double *rows, int i, double s, double t) {
-    *(f64x2 *)(rows + 4 * (size_t)i) = f64x2{s, t};
+__device__ __forceinline__ f64x2 row_lt(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i); }
+__device__ __forceinline__ f64x2 row_us(const double *rows, int i) { return *(const f64x2 *)(rows + 4 * (size_t)i + 2); }
+__device__ __forceinline__ void set_lt(double *rows, int i, double l, double t) {
+    *(f64x2 *)(rows + 4 * (size_t)i) = f64x2{l, t};
 }
-__device__ __forceinline__ void set_un(double *rows, int i, double u, double n) {
-    *(f64x2 *)(rows + 4 * (size_t)i + 2) = f64x2{u, n};
+__device__ __forceinline__ void set_us(double *rows, int i, double u, double s) {
+    *(f64x2 *)(rows + 4 * (size_t)i + 2) = f64x2{u, s};
 }
-enum { kS = 0, kT = 1, kU = 2, kN = 3 };
+enum { kL = 0, kT = 1, kU = 2, kS = 3 };
 __device__ __forceinline__ double &row_at(double *rows, int i, int k) { return rows[4 * (size_t)i + k]; }
 struct TreeRecs {
-    const char *children, *more, *fold, *elim;
+    const char *children, *more, *kid, *fold, *elim;
     const int *rf, *re;
     int nr;
 };
 constexpr int kBatch = 2;   // loop iterations whose loads are issued together
+constexpr int kRowsMax = 3; // rows of a unit in LDS for each thread (kCableLdsUnitMax of 1024)
 // What the first kBatch rows of a thread keep from the assembly for the
 // voltage update.
 struct TreeKeep {
@@ -892,29 +901,34 @@ __device__ __forceinline__ void tree_copied() { asm volatile("s_waitcnt vmcnt(0)
 // A unit's tables at `at`, which stands for the block's byte `from`.
 __device__ __forceinline__ TreeRecs tree_recs(const TreeUnit &u, const char *at, int from) {
     const char *b = at - from;
-    return TreeRecs{b, b + u.o_more, b + u.o_fold, b + u.o_elim, (const int *)(b + u.o_rf), (const int *)(b + u.o_re), u.nr};
+    return TreeRecs{b, b + u.o_more, b + u.o_kid, b + u.o_fold, b + u.o_elim, (const int *)(b + u.o_rf), (const int *)(b + u.o_re), u.nr};
 }
 __device__ __forceinline__ double *tree_rows(char *lds, int np) {
     double *rows = (double *)lds;
     if (threadIdx.x == 0) {
-        set_st(rows, np, 1.0, 0.0);
-        set_un(rows, np, 0.0, 0.0);
+        set_lt(rows, np, 0.0, 0.0);
+        set_us(rows, np, 0.0, 1.0);
     }
     return rows;
 }
 
-// Next row of a list; `m` becomes -1 at its end.
-template <bool LDS> __device__ __forceinline__ int more_row(const TreeRecs &rc, int &m) {
-    if constexpr (LDS) {
-        const unsigned x = ((const unsigned short *)rc.more)[m];
-        m = (x & 0x8000u) ? -1 : m + 1;
-        return (int)(x & 0xfffu);
-    } else {
-        const unsigned x = ((const unsigned *)rc.more)[m];
-        m = (x & kMoreLast) ? -1 : m + 1;
-        return (int)(x & ~kMoreLast);
+// The rows of a list, of which the next entry is read ahead (an entry follows the
+// last list).
+template <bool LDS> struct TreeList {
+    const char *more;
+    int m;   // -1 at its end
+    unsigned e;
+    __device__ __forceinline__ TreeList(const TreeRecs &rc, int first) : more(rc.more), m(first), e(first >= 0 ? at(first) : 0u) {}
+    __device__ __forceinline__ unsigned at(int i) const {
+        return LDS ? ((const unsigned short *)more)[i] : ((const unsigned *)more)[i];
     }
-}
+    __device__ __forceinline__ int next() {
+        const unsigned last = LDS ? 0x8000u : kMoreLast, x = e;
+        e = at(m + 1);
+        m = (x & last) ? -1 : m + 1;
+        return (int)(LDS ? x & 0xfffu : x & ~kMoreLast);
+    }
+};
 // First child of a row and the list of the others, -1 without.
 template <bool LDS> __device__ __forceinline__ void children_of(const TreeRecs &rc, int i, int &ch, int &m) {
     if constexpr (LDS) {
@@ -929,54 +943,81 @@ template <bool LDS> __device__ __forceinline__ void children_of(const TreeRecs &
     }
 }
 
-// Folds the eliminated neighbours of one surviving row.  N of an eliminated
-// row is written by its child's thread and read by nobody before the walk
-// back.  All neighbours are read before any is used: the chain through a round
-// is one LDS read, one reciprocal and one LDS write.
-__device__ __forceinline__ void fold_packed(double *r, const TreeRecs &rc, unsigned long long w, int np) {
+// Folds the eliminated neighbours of one surviving row.  All neighbours are read
+// before any is used, what the reciprocals need first: the chain through a round
+// is one LDS read, one reciprocal and one LDS write.  N of its eliminated parent,
+// the row's old coupling, has its place where the parent's S is until the round
+// ends: it is returned and written in the next one (without a parent: S of the row
+// that stands for it, as it is).
+struct TreeNext {
+    int p;
+    double n;
+};
+__device__ __forceinline__ void put_next(double *r, const TreeNext &x) { row_at(r, x.p, kS) = x.n; }
+__device__ __forceinline__ TreeNext fold_packed(double *r, const TreeRecs &rc, unsigned long long w, int np) {
     const int t = (int)(w & 0xfff), p = (int)((w >> 12) & 0xfff), c = (int)((w >> 24) & 0xfff);
     const int d = (int)((w >> 36) & 0xfff);
     int m = (int)(w >> 48) == (int)kMoreNone ? -1 : (int)(w >> 48);
-    const f64x2 st = row_st(r, t), sc = row_st(r, c), sd = row_st(r, d), sp = row_st(r, p);
-    const double ut = row_at(r, t, kU), uc = row_at(r, c, kU), ud = row_at(r, d, kU), up = row_at(r, p, kU);
+    const f64x2 uc = row_us(r, c), ud = row_us(r, d), up = row_us(r, p), ut = row_us(r, t);
+    const f64x2 lt = row_lt(r, t), lc = row_lt(r, c), ld = row_lt(r, d), lp = row_lt(r, p);
     const bool has = p != np;
-    const double u = has ? ut : 0.0;
-    const double fc = uc * rcp_d(sc.x), fd = ud * rcp_d(sd.x), fp = u * rcp_d(sp.x);
-    double S = fma(-u, fp, fma(-ud, fd, fma(-uc, fc, st.x)));
-    double T = fma(fp, sp.y, fma(fd, sd.y, fma(fc, sc.y, st.y)));
-    while (m >= 0) {
-        const int i = more_row<true>(rc, m);
-        const f64x2 si = row_st(r, i);
-        const double ui = row_at(r, i, kU), f = ui * rcp_d(si.x);
-        S = fma(-ui, f, S);
-        T = fma(f, si.y, T);
+    const double u = has ? ut.x : 0.0;
+    const double fc = uc.x * rcp_d(uc.y), fd = ud.x * rcp_d(ud.y), fp = u * rcp_d(up.y);
+    double S = fma(-u, fp, fma(-ud.x, fd, fma(-uc.x, fc, ut.y)));
+    double L = fma(fp, lp.x, fma(fd, ld.x, fma(fc, lc.x, lt.x)));
+    double T = fma(fp, lp.y, fma(fd, ld.y, fma(fc, lc.y, lt.y)));
+    for (TreeList<true> more(rc, m); more.m >= 0;) {
+        const int i = more.next();
+        const f64x2 li = row_lt(r, i), ui = row_us(r, i);
+        const double f = ui.x * rcp_d(ui.y);
+        S = fma(-ui.x, f, S);
+        L = fma(f, li.x, L);
+        T = fma(f, li.y, T);
     }
-    set_st(r, t, S, T);
-    row_at(r, t, kU) = has ? fp * up : ut;
-    row_at(r, p, kN) = ut;   // without a parent: the row that stands for it, whose N nobody reads
+    set_lt(r, t, L, T);
+    set_us(r, t, has ? fp * up.x : ut.x, S);
+    return TreeNext{p, has ? ut.x : 1.0};
 }
-__device__ __forceinline__ void fold_wide(double *r, const TreeRecs &rc, int q) {
-    const int4 w = ((const int4 *)rc.fold)[q];
-    const int t = w.x, p = w.y;
-    const f64x2 st = row_st(r, t);
-    double S = st.x, T = st.y;
-    auto child = [&](int i) {
-        const f64x2 si = row_st(r, i);
-        const double u = row_at(r, i, kU), f = u * rcp_d(si.x);
+// In global memory every N has a place of its own.  The reads of a record apart
+// from the rest, so that a thread has two records' in flight.
+struct TreeWide {
+    int4 w;
+    f64x2 lt, ut, lc, uc, lp, up;
+};
+__device__ __forceinline__ TreeWide read_wide(const double *r, const TreeRecs &rc, int q) {
+    TreeWide x;
+    x.w = ((const int4 *)rc.fold)[q];
+    const int c = x.w.z >= 0 ? x.w.z : x.w.x, p = x.w.y >= 0 ? x.w.y : x.w.x;
+    x.lt = row_lt(r, x.w.x);
+    x.ut = row_us(r, x.w.x);
+    x.lc = row_lt(r, c);
+    x.uc = row_us(r, c);
+    x.lp = row_lt(r, p);
+    x.up = row_us(r, p);
+    return x;
+}
+__device__ __forceinline__ void fold_wide(double *r, double *n, const TreeRecs &rc, const TreeWide &x) {
+    const int t = x.w.x, p = x.w.y;
+    double L = x.lt.x, T = x.lt.y, U = x.ut.x, S = x.ut.y;
+    auto pass = [&](double u, double s, f64x2 l) {
+        const double f = u * rcp_d(s);
         S = fma(-u, f, S);
-        T = fma(f, si.y, T);
+        L = fma(f, l.x, L);
+        T = fma(f, l.y, T);
+        return f;
     };
-    if (w.z >= 0) child(w.z);
-    for (int m = w.w; m >= 0;) child(more_row<false>(rc, m));
-    if (p >= 0) {
-        const f64x2 sp = row_st(r, p);
-        const double u = row_at(r, t, kU), f = u * rcp_d(sp.x);
-        S = fma(-u, f, S);
-        T = fma(f, sp.y, T);
-        row_at(r, p, kN) = u;
-        row_at(r, t, kU) = f * row_at(r, p, kU);
+    if (x.w.z >= 0) pass(x.uc.x, x.uc.y, x.lc);
+    for (TreeList<false> more(rc, x.w.w); more.m >= 0;) {
+        const int i = more.next();
+        const f64x2 ui = row_us(r, i);
+        pass(ui.x, ui.y, row_lt(r, i));
     }
-    set_st(r, t, S, T);
+    if (p >= 0) {
+        n[p] = U;
+        U = pass(U, x.up.y, x.lp) * x.up.x;
+    }
+    set_lt(r, t, L, T);
+    set_us(r, t, U, S);
 }
 
 // The boundaries of a unit's rounds, one per lane of every wave (a unit in LDS
@@ -986,52 +1027,78 @@ __device__ __forceinline__ int bound_at(int b, int j) { return __builtin_amdgcn_
 
 // All rounds of a unit.  In LDS the next round's record is read before the
 // barrier, so that it is there when the round starts.
-template <bool LDS> __device__ __forceinline__ void tree_up(double *r, const TreeRecs &rc, int np) {
+template <bool LDS> __device__ __forceinline__ void tree_up(double *r, double *n, const TreeRecs &rc, int np) {
     const int tid = (int)threadIdx.x, B = (int)blockDim.x;
     if constexpr (LDS) {
         const unsigned long long *rec = (const unsigned long long *)rc.fold;
         const int bnd = tree_bounds(rc.rf, rc.nr), last = bound_at(bnd, rc.nr);
-        auto rounds = [&](int j, int stride, auto done, auto sync) {
-            int lo = bound_at(bnd, j), q = lo + tid;
-            unsigned long long w = rec[min(q, last - 1)];
-            for (; !done(j); ++j) {
+        const TreeNext none{np, 1.0};
+        int j = 0;
+        {
+            // by all waves, up to two records a thread (kCableLdsUnitMax)
+            auto few = [&](int i) { return i == rc.nr || bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave; };
+            TreeNext n1 = none, n2 = none;
+            int q = tid;
+            unsigned long long w = rec[min(q, max(last - 1, 0))];
+            for (; !few(j); ++j) {
                 const int hi = bound_at(bnd, j + 1);
                 const unsigned long long next = rec[min(hi + tid, last - 1)];
-                if (q < hi) fold_packed(r, rc, w, np);
-                for (q += stride; q < hi; q += stride) fold_packed(r, rc, rec[q], np);
-                sync();
+                TreeNext m1 = none, m2 = none;
+                if (q < hi) m1 = fold_packed(r, rc, w, np);
+                if (q + B < hi) m2 = fold_packed(r, rc, rec[q + B], np);
+                put_next(r, n1);
+                put_next(r, n2);
+                n1 = m1;
+                n2 = m2;
+                tree_barrier<true>();
                 q = hi + tid;
                 w = next;
             }
-            return j;
-        };
-        int j = 0;
-        if (rc.nr > 0) {
-            auto tail = [&](int i) {
-                return i == rc.nr || bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave;
-            };
-            j = rounds(0, B, tail, [] { tree_barrier<true>(); });
-            if (tid < 64 && j < rc.nr) rounds(j, 64, [&](int i) { return i == rc.nr; }, [] { wave_order(); });
+            put_next(r, n1);
+            put_next(r, n2);
+        }
+        if (tid < 64 && j < rc.nr) {
+            // by one wave; lanes past a round's records do its last one once more
+            auto word = [&](int i) { return rec[min(bound_at(bnd, i) + tid, bound_at(bnd, min(i + 1, rc.nr)) - 1)]; };
+            TreeNext n = none;
+            unsigned long long w = word(j);
+            for (; j < rc.nr; ++j) {
+                const unsigned long long next = word(j + 1);
+                const TreeNext m = fold_packed(r, rc, w, np);
+                put_next(r, n);
+                n = m;
+                wave_order();
+                w = next;
+            }
+            put_next(r, n);
         }
         tree_barrier<true>();
     } else {
         for (int j = 0; j < rc.nr; ++j) {
             const int hi = uni(rc.rf[j + 1]);
-            for (int q = uni(rc.rf[j]) + tid; q < hi; q += B) fold_wide(r, rc, q);
+            for (int q = uni(rc.rf[j]) + tid; q < hi; q += 2 * B) {
+                const TreeWide x = read_wide(r, rc, q), y = read_wide(r, rc, min(q + B, hi - 1));
+                fold_wide(r, n, rc, x);
+                if (q + B < hi) fold_wide(r, n, rc, y);
+            }
             tree_barrier<false>();
         }
     }
 }
 
-// T, U and N become T/S, U/S and N/S.
-__device__ __forceinline__ void tree_quotient(const double *from, double *to, int i) {
-    const f64x2 st = row_st(from, i), un = row_un(from, i);
-    const double f = rcp_d(st.x);
-    set_st(to, i, st.x, fdiv(st.y, st.x));
-    set_un(to, i, un.x * f, un.y * f);
+// T, U and N become T/S, U/S and N/S, with S the sum of L and the couplings.
+template <bool LDS>
+__device__ __forceinline__ void tree_quotient(const double *from, double *to, const double *n, const TreeRecs &rc, int i) {
+    const f64x2 lt = row_lt(from, i), us = row_us(from, i);
+    double x;
+    if constexpr (LDS) x = ((const unsigned *)rc.kid)[i >> 5] >> (i & 31) & 1 ? us.y : 0.0;
+    else x = n[i];
+    const double s = lt.x + (us.x + x), f = rcp_d(s);
+    set_lt(to, i, lt.x, fdiv(lt.y, s));
+    set_us(to, i, us.x * f, x * f);
 }
-template <bool LDS> __device__ __forceinline__ void tree_quotients(double *r, int n) {
-    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) tree_quotient(r, r, i);
+template <bool LDS> __device__ __forceinline__ void tree_quotients(double *r, const double *n, const TreeRecs &rc, int np) {
+    for (int i = (int)threadIdx.x; i < np; i += (int)blockDim.x) tree_quotient<LDS>(r, r, n, rc, i);
     tree_barrier<LDS>();
 }
 
@@ -1049,13 +1116,12 @@ template <bool LDS> __device__ __forceinline__ void tree_down(double *r, const T
             int i, p, c;
             double x, u, n;
         };
-        auto word = [&](int j) { return rec[min(bound_at(bnd, max(j, 0)) + tid, last - 1)]; };
         auto load = [&](unsigned long long w) {
             Row s;
             s.i = (int)(w & 0xfff);
             s.p = (int)((w >> 12) & 0xfff);
             s.c = (int)((w >> 24) & 0xfff);
-            const f64x2 un = row_un(r, s.i);
+            const f64x2 un = row_us(r, s.i);
             s.x = row_at(r, s.i, kT);
             s.u = un.x;
             s.n = un.y;
@@ -1064,33 +1130,48 @@ template <bool LDS> __device__ __forceinline__ void tree_down(double *r, const T
         auto one = [&](const Row &s) {
             row_at(r, s.i, kT) = fma(s.n, row_at(r, s.c, kT), fma(s.u, row_at(r, s.p, kT), s.x));
         };
-        auto rounds = [&](int j, int stride, auto done, auto sync) {
-            unsigned long long w1 = word(j - 1);
-            Row row = load(word(j));
-            for (; !done(j); --j) {
-                const int lo = bound_at(bnd, j), hi = bound_at(bnd, j + 1);
-                const unsigned long long w2 = word(j - 2);
+        auto small = [&](int i) { return bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave; };
+        int j = rc.nr - 1;
+        if (tid < 64) {
+            // by one wave; lanes past a round's records do its last one once more
+            auto word = [&](int i) {
+                const int k = max(i, 0);
+                return rec[min(bound_at(bnd, k) + tid, bound_at(bnd, k + 1) - 1)];
+            };
+            int k = j;
+            unsigned long long w1 = word(k - 1);
+            Row row = load(word(k));
+            for (; k >= 0 && small(k); --k) {
+                const unsigned long long w2 = word(k - 2);
                 const Row next = load(w1);
-                if (lo + tid < hi) one(row);
-                for (int q = lo + tid + stride; q < hi; q += stride) one(load(rec[q]));
-                sync();
+                one(row);
+                wave_order();
                 row = next;
                 w1 = w2;
             }
-            return j;
-        };
-        auto small = [&](int i) { return bound_at(bnd, i + 1) - bound_at(bnd, i) <= kTreeWave; };
-        int j = rc.nr - 1;
-        if (tid < 64) rounds(j, 64, [&](int i) { return i < 0 || !small(i); }, [] { wave_order(); });
+        }
         while (j >= 0 && small(j)) --j;
         tree_barrier<true>();
-        if (j >= 0) rounds(j, B, [](int i) { return i < 0; }, [] { tree_barrier<true>(); });
+        if (j < 0) return;
+        auto word = [&](int i) { return rec[min(bound_at(bnd, max(i, 0)) + tid, last - 1)]; };
+        unsigned long long w1 = word(j - 1);
+        Row row = load(word(j));
+        for (; j >= 0; --j) {
+            const int lo = bound_at(bnd, j), hi = bound_at(bnd, j + 1);
+            const unsigned long long w2 = word(j - 2);
+            const Row next = load(w1);
+            if (lo + tid < hi) one(row);
+            for (int q = lo + tid + B; q < hi; q += B) one(load(rec[q]));
+            tree_barrier<true>();
+            row = next;
+            w1 = w2;
+        }
     } else {
         for (int j = rc.nr - 1; j >= 0; --j) {
             const int hi = uni(rc.re[j + 1]);
             for (int q = uni(rc.re[j]) + tid; q < hi; q += B) {
                 const int4 w = ((const int4 *)rc.elim)[q];
-                const f64x2 un = row_un(r, w.x);
+                const f64x2 un = row_us(r, w.x);
                 double x = fma(un.x, row_at(r, w.y, kT), row_at(r, w.x, kT));
                 if (w.z != w.x) x = fma(un.y, row_at(r, w.z, kT), x);
                 row_at(r, w.x, kT) = x;
@@ -1101,10 +1182,10 @@ template <bool LDS> __device__ __forceinline__ void tree_down(double *r, const T
 }
 
 // The rows of a unit from this step's v, rhs, d and cm; ghosts (TAKE) bring
-// the rows that their pieces handed over.  A row's currents to its children
-// come from the children's rows, which leave them in N.
+// the rows that their pieces handed over.  A row's currents to its children come
+// from the children's rows, which leave them where S (in global memory N) will be.
 template <bool LDS, bool TAKE>
-__device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev &nd, const GlobDev &g, double *r,
+__device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev &nd, const GlobDev &g, double *r, double *N,
                                               const TreeRecs &rc, int p0, int np, TreeKeep &keep) {
     const int tid = (int)threadIdx.x, B = (int)blockDim.x;
     for (int i0 = tid; i0 < np; i0 += kBatch * B) {
@@ -1127,9 +1208,9 @@ __device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev 
                 v[k] = nd.v[n];
                 vp[k] = nd.v[w[k].y >= 0 ? w[k].y : n];
                 if (TAKE && w[k].z >= 0) {
-                    const f64x2 st = row_st(c.G, w[k].z);
-                    y[k] = st.x;
-                    x[k] = st.y;
+                    const f64x2 lt = row_lt(c.G, w[k].z);
+                    y[k] = lt.x;
+                    x[k] = lt.y;
                 } else {
                     x[k] = nd.rhs[n];
                     y[k] = nd.d[n];
@@ -1142,9 +1223,9 @@ __device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev 
             if (i < np) {
                 const double f = gu[k] * (vp[k] - v[k]);
                 const bool ghost = TAKE && w[k].z >= 0;
-                set_st(r, i, ghost ? y[k] : fma(a[k], 1e-3 * cm[k] / g.dt + y[k], gu[k]),
-                       ghost ? x[k] : fma(a[k], x[k], f));
-                set_un(r, i, gu[k], w[k].w == -1 ? f : 0.0);
+                set_lt(r, i, ghost ? y[k] : a[k] * (1e-3 * cm[k] / g.dt + y[k]), ghost ? x[k] : fma(a[k], x[k], f));
+                set_us(r, i, gu[k], f);
+                if constexpr (!LDS) N[i] = w[k].w == -1 ? f : 0.0;
                 if (i0 == tid) {
                     keep.n[k] = w[k].x;
                     keep.src[k] = w[k].z;
@@ -1155,20 +1236,37 @@ __device__ __forceinline__ void tree_assemble(const CableDev &c, const NodesDev 
     }
     tree_copied();
     tree_barrier<LDS>();
-    for (int i = tid; i < np; i += B) {
+    // T without the currents to the children, and S
+    auto own = [&](int i) {
         int ch, m;
         children_of<LDS>(rc, i, ch, m);
-        if (ch < 0) continue;
-        f64x2 st = row_st(r, i);
-        for (;;) {
-            const f64x2 un = row_un(r, ch);
-            st.x += un.x;
-            st.y -= un.y;
-            row_at(r, ch, kN) = 0.0;
-            if (m < 0) break;
-            ch = more_row<LDS>(rc, m);
+        double T = row_at(r, i, kT), S = row_at(r, i, kL) + row_at(r, i, kU);
+        TreeList<LDS> more(rc, m);
+        while (ch >= 0) {
+            S += row_at(r, ch, kU);
+            if constexpr (LDS) {
+                T -= row_at(r, ch, kS);
+            } else {
+                T -= N[ch];
+                N[ch] = 0.0;
+            }
+            ch = more.m >= 0 ? more.next() : -1;
         }
-        set_st(r, i, st.x, st.y);
+        row_at(r, i, kT) = T;
+        return S;
+    };
+    if constexpr (LDS) {
+        // a row's S replaces what its parent's thread reads
+        double S[kRowsMax];
+#pragma unroll
+        for (int k = 0; k < kRowsMax; ++k)
+            if (tid + k * B < np) S[k] = own(tid + k * B);
+        tree_barrier<true>();
+#pragma unroll
+        for (int k = 0; k < kRowsMax; ++k)
+            if (tid + k * B < np) row_at(r, tid + k * B, kS) = S[k];
+    } else {
+        for (int i = tid; i < np; i += B) row_at(r, i, kS) = own(i);
     }
     tree_barrier<LDS>();
 }
@@ -1215,28 +1313,29 @@ __global__ __launch_bounds__(1024) void k_tree_a(CableDev c, NodesDev nd, GlobDe
     const int tid = (int)threadIdx.x, B = (int)blockDim.x, p0 = u.p0, np = u.np;
     double *r = tree_rows(tree_lds, np);
     char *tab = tree_lds + tree_row_bytes(np);
-    tree_copy(tab, c.block + 16 * (size_t)u.block, tree_up_bytes(u.mode, u.bytes, u.o_re, u.o_fold));
+    tree_copy(tab, c.block + 16 * (size_t)u.block, tree_up_bytes(u.mode, u.bytes, u.o_re, u.o_kid));
     const TreeRecs rc = tree_recs(u, tab, 0);
     TreeKeep keep;
-    tree_assemble<true, false>(c, nd, g, r, rc, p0, np, keep);
+    tree_assemble<true, false>(c, nd, g, r, nullptr, rc, p0, np, keep);
     double *out = c.G + 4 * (size_t)p0;
     if (u.mode == kUnitTop) {
         for (int i = tid; i < np; i += B) {
-            const f64x2 st = row_st(r, i);
-            set_st(out, i, st.x, st.y);
+            const f64x2 lt = row_lt(r, i), us = row_us(r, i);
+            set_lt(out, i, lt.x, lt.y);
+            set_us(out, i, us.x, us.y);
         }
         return;
     }
-    tree_up<true>(r, rc, np);
+    tree_up<true>(r, nullptr, rc, np);
     if (u.mode == kUnitPiece) {
         // a root's row stays as it is, for its trunk
         for (int i = tid; i < np; i += B) {
-            tree_quotient(r, out, i);
+            tree_quotient<true>(r, out, nullptr, rc, i);
             if (c.pos[p0 + i].w != -1) row_at(out, i, kT) = row_at(r, i, kT);
         }
         return;
     }
-    tree_quotients<true>(r, np);
+    tree_quotients<true>(r, nullptr, rc, np);
     tree_down<true>(r, rc);
     tree_voltage<false>(c, nd, g, r, p0, np, keep);
 }
@@ -1247,7 +1346,7 @@ __global__ __launch_bounds__(1024) void k_tree_top(CableDev c, NodesDev nd, Glob
     extern __shared__ __align__(16) char tree_lds[];
     const TreeUnit u = units[blockIdx.x];
     const char *block = c.block + 16 * (size_t)u.block;
-    double *r;
+    double *r, *n = nullptr;
     TreeRecs rc;
     if constexpr (LDS) {
         r = tree_rows(tree_lds, u.np);
@@ -1256,12 +1355,13 @@ __global__ __launch_bounds__(1024) void k_tree_top(CableDev c, NodesDev nd, Glob
         rc = tree_recs(u, tab, 0);
     } else {
         r = c.G + 4 * (size_t)u.p0;
+        n = c.N + u.p0;
         rc = tree_recs(u, block, 0);
     }
     TreeKeep keep;
-    tree_assemble<LDS, true>(c, nd, g, r, rc, u.p0, u.np, keep);
-    tree_up<LDS>(r, rc, u.np);
-    tree_quotients<LDS>(r, u.np);
+    tree_assemble<LDS, true>(c, nd, g, r, n, rc, u.p0, u.np, keep);
+    tree_up<LDS>(r, n, rc, u.np);
+    tree_quotients<LDS>(r, n, rc, u.np);
     tree_down<LDS>(r, rc);
     tree_voltage<true>(c, nd, g, r, u.p0, u.np, keep);
 }
@@ -1305,17 +1405,18 @@ __global__ __launch_bounds__(1024) void k_tree_b(CableDev c, NodesDev nd, GlobDe
         const TreeRecs rc = tree_recs(t, tab, 0);
         for (int i = tid; i < nt; i += B) {
             const int src = c.pos[t.p0 + i].z;
-            const f64x2 st = row_st(c.G, src >= 0 ? src : t.p0 + i);
-            set_st(r, i, st.x, st.y);
-            set_un(r, i, c.pu[t.p0 + i], 0.0);
+            const f64x2 lt = row_lt(c.G, src >= 0 ? src : t.p0 + i);
+            const f64x2 us = row_us(c.G, t.p0 + i);
+            set_lt(r, i, lt.x, lt.y);
+            set_us(r, i, us.x, src >= 0 ? lt.x + us.x : us.y);
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k)
             if (tid + k * B < np) keep.v[k] = nd.v[keep.n[k]];
         tree_copied();
         tree_barrier<true>();
-        tree_up<true>(r, rc, nt);
-        tree_quotients<true>(r, nt);
+        tree_up<true>(r, nullptr, rc, nt);
+        tree_quotients<true>(r, nullptr, rc, nt);
         tree_down<true>(r, rc);
         if (!piece) {
             tree_voltage<false>(c, nd, g, r, p0, nt, keep);

@@ -95,7 +95,7 @@ struct SlotHost {
 // cut alone.
 enum {
     kCabParent, kCabPos, kCabUnits, kCabUnitsA, kCabUnitsTop, kCabUnitsTopG, kCabUnitsB, kCabBlock, kCabUploaded,
-    kCabPa = kCabUploaded, kCabPu, kCabG, kCabArrays
+    kCabPa = kCabUploaded, kCabPu, kCabG, kCabN, kCabArrays
 };
 size_t cable_layout(const CableHost &h, int64_t N, size_t *offs) {
     const size_t P = h.pos_node.size(), U = h.unit_mode.size();
@@ -110,6 +110,7 @@ size_t cable_layout(const CableHost &h, int64_t N, size_t *offs) {
         bytes[kCabBlock] += table_bound((size_t)(h.unit_pos[u + 1] - h.unit_pos[u]), wide[u]);
     bytes[kCabPa] = bytes[kCabPu] = 8 * P;
     bytes[kCabG] = 32 * P;
+    bytes[kCabN] = h.list_top_g.empty() ? 0 : 8 * P;
     size_t off = 0;
     for (int j = 0; j < kCabArrays; ++j) {
         offs[j] = off;
@@ -1163,6 +1164,7 @@ int mech_bind_cable(mech_ctx *c, const int32_t *parent, const double *g_axial, i
     d.pa = D(kCabPa);
     d.pu = D(kCabPu);
     d.G = D(kCabG);
+    d.N = D(kCabN);
     if (c->n_nodes > 0) {
         if (!c->nd.area) return fail(c, MECH_ERR_STATE, "bind area (mech_bind_nodes) before mech_bind_cable");
         HIPCHK(c, launch_cable_coeffs(d, c->nd.area, c->stream));

@@ -18,15 +18,18 @@ namespace mech {
 // its trunk's unit.
 enum { kUnitFull = 0, kUnitPiece = 1, kUnitTop = 2 };
 
-// LDS of a unit solved there: per position and at most four doubles of its
-// row, its children (4 B), an elimination record (8 B), two fold records (8 B
-// each; a row that is eliminated changes at most two others) and two list
-// entries (2 B each); and the round boundaries and padding.
+// LDS of a unit solved there: per position the four doubles of its row, its
+// children (4 B), an elimination record (8 B), two fold records (8 B each; a row
+// that is eliminated changes at most two others), a list entry (2 B; where it
+// takes a second one, it changes one row less) and a bit; and the round
+// boundaries and padding.
 constexpr int kCableLdsBytesPerNode = 64;
 constexpr int kCableLdsFixed = 1024;
 // Records of a unit in LDS hold 12-bit rows; its children entries take 0xfff
-// for no row, its other records the row after its last.
-constexpr int kCableLdsUnitMax = 4094;
+// for no row, its other records the row after its last.  A round of e rows has at
+// most 2e fold records and one for each row left, so at most two thirds of a
+// unit's rows: two for each of 1024 threads.
+constexpr int kCableLdsUnitMax = 3071;
 constexpr int kNoRow = 0xfff;
 // An elimination round of at most this many records is run by one wave, which
 // needs no workgroup barrier.
@@ -228,6 +231,9 @@ inline std::string build_cable(int64_t N, const int32_t *parent, int cap, CableH
 // further children in `more` or -1), `elim` records (row, parent, child or
 // the row itself); `more` entries hold a row and, in the top bit, whether the
 // list ends.
+// `kid` marks the rows that have a child left when they are eliminated: in a
+// unit's rows in LDS the coupling to it takes the place of the pivot then, and the
+// others' pivots stay there.
 struct FoldRec { int32_t t, parent, child, more; };
 struct ElimRec { int32_t i, p, c; };
 // On the device a unit's tables are one block of memory (tree_tables below).
@@ -266,6 +272,7 @@ struct TreeSchedule {
     // per position: its first child in the unit (or -1) and the further
     // children's index in more (unit-relative, or -1), for the axial currents
     std::vector<int32_t> child, child_more;
+    std::vector<char> kid;   // per position
 };
 
 inline void build_schedule(const CableHost &h, TreeSchedule &s) {
@@ -274,6 +281,7 @@ inline void build_schedule(const CableHost &h, TreeSchedule &s) {
     const size_t P = h.pos_node.size();
     s.child.assign(P, -1);
     s.child_more.assign(P, -1);
+    s.kid.assign(P, 0);
     s.fold.reserve(P + P / 8);
     s.elim.reserve(P);
     s.unit_rnd.push_back(0);
@@ -348,6 +356,7 @@ inline void build_schedule(const CableHost &h, TreeSchedule &s) {
             for (int i : sel) {
                 const int p = cp[i], c = nch[i] == 1 ? xr[i] : -1;
                 s.elim.push_back({i, p, c >= 0 ? c : i});
+                s.kid[p0 + i] = c >= 0;
                 if (mark[p] == round) {
                     mark[p] = n + round;
                     touched.push_back(p);
@@ -389,16 +398,18 @@ inline void build_schedule(const CableHost &h, TreeSchedule &s) {
 
 // A unit as a workgroup finds it: one 64-byte read.  Its block holds, each at
 // a multiple of 16 bytes: the children of every row (o_more bytes), the lists
-// (up to o_fold), the fold records (up to o_rf), the round boundaries of the
-// fold (up to o_re) and of the elimination records (up to o_elim), the
-// elimination records (up to bytes). 
+// (up to o_kid), a bit a row, in 32-bit words, for the rows marked in `kid` (up
+// to o_fold; none in a trunk with rows in global memory), the fold records (up to
+// o_rf), the round boundaries of the fold (up to o_re) and of the elimination
+// records (up to o_elim), the elimination records (up to bytes).
 struct TreeUnit {
     int32_t p0, np, mode, nr;
     int32_t block;   // in units of 16 bytes
     int32_t o_more, o_fold, o_rf, o_re, o_elim, bytes;
     int32_t solves_trunk;   // piece: solves its cell's trunk itself
     int32_t wide;           // rows in global memory
-    int32_t unused[3];
+    int32_t o_kid;
+    int32_t unused[2];
 };
 struct TreeTables {
     std::vector<TreeUnit> unit;
@@ -413,7 +424,7 @@ inline std::vector<char> wide_units(const CableHost &h) {
 // Bytes that a unit's block takes at most.
 inline size_t table_bound(size_t rows, bool wide) {
     const size_t rounds = std::min<size_t>(rows, kTreeRounds + 1);
-    return rows * (wide ? 8 + 8 + 32 + 16 : 4 + 4 + 16 + 8) + 8 * rounds + 6 * 16;
+    return rows * (wide ? 8 + 8 + 32 + 16 : 4 + 2 + 16 + 8) + (rows / 32 + 1) * 4 + 8 * rounds + 8 * 16;
 }
 inline void tree_tables(const CableHost &h, const TreeSchedule &s, TreeTables &d) {
     d = TreeTables();
@@ -453,6 +464,14 @@ inline void tree_tables(const CableHost &h, const TreeSchedule &s, TreeTables &d
             if (w) put(&x, 4);
             else put(&y, 2);
         }
+        const uint32_t past = 0;   // read, not used, behind the last entry
+        put(&past, w ? 4 : 2);
+        t.o_kid = close();
+        for (int i = 0; !w && i < t.np; i += 32) {
+            uint32_t x = 0;
+            for (int k = i; k < std::min(i + 32, t.np); ++k) x |= (uint32_t)s.kid[t.p0 + k] << (k - i);
+            put(&x, 4);
+        }
         t.o_fold = close();
         for (int q = s.rnd_fold[a]; q < s.rnd_fold[b]; ++q) {
             const uint64_t x = pack_fold(s.fold[q], s.more.data() + s.unit_more[u], t.np);
@@ -481,7 +500,7 @@ inline void tree_tables(const CableHost &h, const TreeSchedule &s, TreeTables &d
     }
 }
 
-// LDS bytes of a unit's rows (S, T, U, N each): its own and the one that stands
+// LDS bytes of a unit's rows (L, T, U, S each): its own and the one that stands
 // for a missing neighbour.
 constexpr int tree_row_bytes(int np) { return 32 * (np + 1); }
 // Bytes of a unit's block that the first launch copies to LDS: whole cells need
@@ -489,8 +508,8 @@ constexpr int tree_row_bytes(int np) { return 32 * (np + 1); }
 // last launch takes a piece's block from o_re on).  By value: a reference to the
 // unit kept it in memory on the device, 68 bytes of scratch a lane and 12 % of a
 // solve.
-constexpr int tree_up_bytes(int mode, int bytes, int o_re, int o_fold) {
-    return mode == kUnitFull ? bytes : mode == kUnitPiece ? o_re : o_fold;
+constexpr int tree_up_bytes(int mode, int bytes, int o_re, int o_kid) {
+    return mode == kUnitFull ? bytes : mode == kUnitPiece ? o_re : o_kid;
 }
 
 // What the launches of a solve run, a unit (in `b` a pair) a workgroup, and their
@@ -524,7 +543,7 @@ inline void tree_launches(const CableHost &h, TreeTables &t, size_t lds_bytes, T
     for (int32_t u : h.list_top) shared[u] = alone(t.unit[u]) + piece_max[h.cell_of[u]] <= lds_bytes;
     auto first = [&](const TreeUnit &x) {
         l.a.push_back(x);
-        grow(l.lds_a, (size_t)tree_row_bytes(x.np) + tree_up_bytes(x.mode, x.bytes, x.o_re, x.o_fold));
+        grow(l.lds_a, (size_t)tree_row_bytes(x.np) + tree_up_bytes(x.mode, x.bytes, x.o_re, x.o_kid));
         grow(l.rows_a, (size_t)x.np);
     };
     auto last = [&](const TreeUnit &x, const TreeUnit &trunk, size_t bytes) {
