@@ -16,7 +16,8 @@ namespace mech {
 // about forty vector registers across the fused kernels' loops, which held
 // the FP64 fused kernel at 4 waves per SIMD; these take each coefficient as
 // the scalar operand of the fused multiply-add (fma_s), so the kernels fit
-// in 70 to 80 (FP64) and 55 (FP32-mixed) registers.
+// in 70 to 80 (FP64) and 55 (FP32-mixed) registers, the time-fused ones in 87 to 90
+// and 70.
 
 // a b + c with c in a scalar register pair (one scalar operand is allowed per
 // vector instruction).
@@ -33,14 +34,16 @@ MECH_HD_INLINE double fma_s(double a, double b, double c) {
 // the hardware reciprocal (2^-24.3 measured) and one third-order step, r <- r +
 // r (e + e^2) with e = 1 - b r, whose error is e^3 (two Newton steps, which
 // this replaces, take one operation more and end at the same rounding error).
-// Valid for normal, finite, non-zero b.
-MECH_HD_INLINE double rcp_d(double b) {
+// Valid for normal, finite, non-zero b.  Host builds refine 1/b, or what the
+// seed's test (tests/math_seeds.cpp) puts in its place.
 #if defined(__HIP_DEVICE_COMPILE__)
-    const double r = __builtin_amdgcn_rcp(b), e = fma(-b, r, 1.0);
-    return fma(r, fma(e, e, e), r);
-#else
-    return 1.0 / b;
+#define MECH_RCP_SEED(b) __builtin_amdgcn_rcp(b)
+#elif !defined(MECH_RCP_SEED)
+#define MECH_RCP_SEED(b) (1.0 / (b))
 #endif
+MECH_HD_INLINE double rcp_d(double b) {
+    const double r = MECH_RCP_SEED(b), e = fma(-b, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 // a/b with one residual correction of the quotient, for a/b in the normal
 // range (every rate expression's).
