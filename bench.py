@@ -64,7 +64,7 @@ def alg_bytes_per_step(w, prec: str) -> int:
     return tot
 
 
-KERNEL_SOURCES = ("mech_kernels.hip", "mech_math.h", "mech_internal.h")
+KERNEL_SOURCES = ("mech_kernels.hip", "mech_math.h", "mech_internal.h", "mech_tree.h")
 
 
 def kernel_source_sha256() -> str:
@@ -180,8 +180,9 @@ def time_variant(w, prec, path, steps, warmup, autotune, torch, mech, launch=Non
            "alg_bytes_per_step": alg_bytes_per_step(w, prec), "tuned": tuned, "spikes": spikes,
            "tiles": info["n_tiles"]}
     if path == "batched":
-        out["launches"] = (f"one fused launch per step; the {steps - 1} middle steps replayed from HIP graphs of at "
-                           "most 64 steps, captured before the timed region")
+        out["launches"] = (f"one fused launch per step, the {steps - 1} middle steps replayed from HIP graphs of at "
+                           "most 64 steps, captured before the timed region; in the clamp and isolated modes a "
+                           "context that fits the L2s in its own launch shape takes up to 256 steps a launch instead")
     if path == "resident":
         out["time_fused"] = (f"states stay in LDS for {resident[1]} steps per launch and cross HBM once per "
                              "launch; alg_GBps is the per-step algorithmic bytes over the step time, not HBM "
