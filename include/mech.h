@@ -216,10 +216,10 @@ int mech_cable_required_bytes(int64_t n_nodes, const int32_t *parent, int32_t un
  * unbranched cell).  The library builds the elimination
  * schedules into dev_buf (dev_bytes >=
  * mech_cable_required_bytes, 256-byte aligned, caller owned, MECH_ERR_NOMEM
- * if short) and computes the coupling coefficients 100 g/area from the
- * bound area and g_axial, so area (mech_bind_nodes, MECH_ERR_STATE if not
- * bound) and g_axial must hold their values at this call; bind again after
- * changing either.  cm is read every step.                                 */
+ * if short) and keeps copies of area and g_axial there, so area
+ * (mech_bind_nodes, MECH_ERR_STATE if not bound) and g_axial must hold their
+ * values at this call; bind again after changing either.  cm is read every
+ * step.                                                                    */
 int mech_bind_cable(mech_ctx *ctx, const int32_t *parent, const double *g_axial, int32_t unit_nodes,
                     void *dev_buf, size_t dev_bytes);
 
@@ -309,7 +309,12 @@ int mech_step(mech_ctx *ctx, int64_t nsteps, int64_t k0, double dt, int vmode, i
  * 256 threads with tiles of 2048 instances and 1024 nodes.  Rebuilds the tile
  * table.  BATCHED and RESIDENT results do not depend on the shape
  * (their node sums are order-independent); PLAIN's rhs/d differ from one
- * run to the next by the rounding order of its atomics.                    */
+ * run to the next by the rounding order of its atomics.
+ * mech_get_launch reports the batched path's shape.  Until a shape is set that
+ * is the context's own, which the time-fused path does not have: setting what
+ * was reported leaves the batched path as it is and gives the time-fused path
+ * these tiles.  A context's own shape of the smallest tiles (256 instances) is
+ * reported with 256 threads and launched with up to 512.                   */
 enum { MECH_LAUNCH_XCD_ORDER = 1, MECH_LAUNCH_NONTEMPORAL = 2, MECH_LAUNCH_PLAIN_ATOMIC = 4 };
 int mech_set_launch(mech_ctx *ctx, int block, int tile_instances, int tile_nodes, int blocks_per_cu,
                     int flags);

@@ -818,10 +818,18 @@ __global__ void k_visolated(NodesDev nd, GlobDev g) {
 // in every first step.
 //
 // A unit's rows and records sit in LDS.  What bounds the solve is the chain of
-// dependent rounds and the memory latencies before and after them, not bytes:
-// a round is one LDS read, a reciprocal, an LDS write and a barrier, about
-// 0.2 us.  Rounds with no more records than a wave has lanes are run by one
-// wave without workgroup barriers.
+// dependent rounds and the memory latencies before and after them, not bytes.  A
+// round is one LDS read, a reciprocal, an LDS write and a barrier: 600 to 850
+// cycles (0.3 us), the way back a little less than the way up.  By the shader
+// clock, cycles of a workgroup (medians):
+//   whole cells of 200 to 2000     22.4 k: loads 3.7, tables and children 2.5, 11
+//     rounds 7.9, quotients 0.9, 11 rounds back 7.0, voltage 0.7
+//   pieces of 1024, first launch   29.5 k: loads 13.0 (two workgroups a CU and
+//     all the memory traffic), tables and children 3.8, rounds 9.4, rows out 2.7
+//   pieces, last launch            28.9 k: loads 10.7, the trunk's rounds 4.9 + 4.2,
+//     hand-over 1.3, own rounds back 7.0, voltage 0.9
+// Rounds with no more records than a wave has lanes are run by one wave without
+// workgroup barriers.
 //
 // A cell larger than a unit takes two launches.  In the first, pieces
 // eliminate up to their roots and the trunk's rows are assembled (the only
@@ -834,9 +842,9 @@ __global__ void k_visolated(NodesDev nd, GlobDev g) {
 // own in between, in LDS or, if they are larger than that, with their rows
 // in global memory.
 //
-// Solve of 64 cells of 200 to 20 000 compartments (369 k in all): 36 us a step,
+// Solve of 64 cells of 200 to 20 000 compartments (369 k in all): 34.5 us a step,
 // where elimination by heights in three launches took 88; of 6 cells of 200 to
-// 2000 (5.8 k): 15 us, where it took 48.
+// 2000 (3.4 k): 12.8 us, where it took 48.
 // A row: L, T, U and S side by side, 32 bytes; of an eliminated row with a child
 // left N in place of S.
 typedef double f64x2 __attribute__((ext_vector_type(2)));

@@ -546,10 +546,12 @@ FusedArgs fused_args(mech_ctx *c, const Launch &l, const GlobDev &g, int64_t k, 
 }
 
 // One phase as a call of its own (mech_cur, mech_state): every type in one
-// launch.  The current update needs a tile's contributions in LDS; a context
-// with thousands of instances on one node has a tile that is too large for
-// that and takes a launch per type (as does MECH_LAUNCH_PLAIN_ATOMIC, which
-// asks for that path's scatter).
+// launch.  The current update needs a tile's contributions in LDS (18 B an
+// instance, 26 with the shared calcium ion, 16 + 2 B a type for a node) within the
+// 64 KiB that a launch has without asking.  What needs more takes a launch per
+// type: a context with thousands of instances on one node, and under the shared
+// ion one of six types or more whose own tiles hold 2048 instances on 448 nodes
+// (65 792 B).  So does MECH_LAUNCH_PLAIN_ATOMIC, which asks for that path's scatter.
 constexpr size_t kPhaseLds = 65536;
 int launch_phase(mech_ctx *c, bool cur, int64_t k, const GlobDev &g, int accumulate) {
     const Launch &l = c->own();
@@ -1034,8 +1036,8 @@ int mech_bind_nodes(mech_ctx *c, double *v, double *rhs, double *d, const double
 // The default keeps cells whole where every cell fits LDS, which makes the
 // solve one launch, and cuts at 1024 nodes where one does not (a second launch
 // is then needed anyway, and units of 512 to 2048 nodes solve within 2 % of
-// each other).  Solve of 1000 cells of 1300 compartments: 44 us whole, 82 cut
-// at 1024; 200 of 2000: 20 and 32; 6 of 200 to 2000: 15.1 and 20.5.
+// each other).  Solve of 1000 cells of 1300 compartments: 43 us whole, 81 cut
+// at 1024; 200 of 2000: 19 and 32; 6 of 200 to 2000: 12.8 and 18.8.
 constexpr int kCableFallbackBytes = 65536 - 8192;
 constexpr int kCableDefaultUnit = 1024;
 int cable_cap(int64_t n_nodes, const int32_t *parent, int32_t unit_nodes, int lds_nodes) {
