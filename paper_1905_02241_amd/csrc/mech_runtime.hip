@@ -892,23 +892,28 @@ int mech_alloc(mech_ctx **out, int64_t n_nodes, const mech_type_desc *types, int
             }
         }
     }
-    for (SlotHost &h : c->slots) {
+    for (SlotHost &h : c->slots)
         for (int64_t i = kPad; i < h.n && !h.crossing; i += kPad) h.crossing = h.ni[i] == h.ni[i - 1];
-        for (int64_t i = kLongRun - 1; i < h.n && !h.crowded; ++i) h.crowded = h.ni[i] == h.ni[i - (kLongRun - 1)];
-    }
     {
         // the fused paths sum a node's contributions in fixed point, exact up
         // to kMaxPerNode of them
         std::vector<int32_t> &per = c->per_node;
         per.assign(n_nodes, 0);
+        int32_t most = 0;
         for (const SlotHost &h : c->slots)
-            for (int32_t n : h.ni)
-                if (++per[n] > kMaxPerNode) {
+            for (int32_t n : h.ni) {
+                most = std::max(most, ++per[n]);
+                if (most > kMaxPerNode) {
                     int code = fail(nullptr, MECH_ERR_INVAL, "node %d carries more than %d instances", n,
                                     kMaxPerNode);
                     delete c;
                     return code;
                 }
+            }
+        if (most >= kLongRun)
+            for (SlotHost &h : c->slots)
+                for (int64_t i = kLongRun - 1; i < h.n && !h.crowded; ++i)
+                    h.crowded = h.ni[i] == h.ni[i - (kLongRun - 1)];
     }
     compute_layout(n_nodes, c->slots, prec, c->L);
     if (dev_bytes < c->L.total) {
